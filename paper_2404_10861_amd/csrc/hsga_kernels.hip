@@ -11,6 +11,7 @@
 // contiguous 256-byte wavefront access per plane.
 #include "hsga_device.hpp"
 #include "hsga_internal.hpp"
+#include "hsga_layout.hpp"
 
 namespace hsga {
 
@@ -56,13 +57,16 @@ hipError_t launch_founders(uint32_t* trait, uint32_t* counter, uint32_t* surf, u
 // synchronous simulations can cache placements for a whole
 // subpopulation).  The sites of a launch batch's ingests come from the
 // rule's constant-time tables, one thread per ingest, and the first
-// wavefront writes the run's layout after them (lane = site), for the
-// run-bound queries and the read calls.
+// wavefront writes the run's layout after them (lane = site, S <= 64), for
+// the run-bound queries and the read calls.
 __device__ __forceinline__ void run_sites(const RuleTable* rules, uint32_t kind, uint32_t S,
                                           uint32_t* sites, uint32_t* layout, uint32_t tau0,
                                           uint32_t count, uint32_t k) {
     if (k < count) sites[k] = scheme_site(rules, kind, S, tau0 + k);
-    if (k < S) layout[k] = scheme_item_at(rules, kind, S, (uint64_t)tau0 + count, k);
+    if (k < 64) {
+        const uint32_t item = scheme_layout_wave(rules, kind, S, (uint64_t)tau0 + count);
+        if (k < S) layout[k] = item;
+    }
 }
 
 __global__ __launch_bounds__(256) void run_sites_kernel(const RuleTable* __restrict__ rules,

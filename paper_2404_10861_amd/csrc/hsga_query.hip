@@ -5,6 +5,7 @@
 
 #include "hsga_device.hpp"
 #include "hsga_internal.hpp"
+#include "hsga_layout.hpp"
 
 namespace hsga {
 
@@ -63,7 +64,7 @@ constexpr uint32_t kWsStatusMixed = 1, kWsStatusHorizon = 2;
 __device__ __forceinline__ uint32_t time_rank(uint32_t held, uint32_t lane, uint32_t S) {
     uint32_t rank = 0;
     for (uint32_t q = 0; q < S; ++q) {
-        const uint32_t tq = __shfl(held, (int)q);
+        const uint32_t tq = lane_value(held, q);
         rank += (tq < held || (tq == held && q < lane)) ? 1u : 0u;
     }
     return rank;
@@ -81,7 +82,7 @@ __device__ __forceinline__ uint32_t replay_layout(uint32_t kind, uint32_t S, uin
 // the query has them (constant time per site), else by the replay.
 __device__ __forceinline__ uint32_t layout_lane(const RuleTable* rules, uint32_t kind, uint32_t S,
                                                 uint32_t T, uint32_t lane) {
-    if (rules) return scheme_item_at(rules, kind, S, T, lane);
+    if (rules) return scheme_layout_wave(rules, kind, S, T);
     return replay_layout(kind, S, T, lane);
 }
 
@@ -286,56 +287,150 @@ __global__ __launch_bounds__(64) void mrca_layouts_kernel(Scheme sc,
     }
 }
 
-// General route, all ordered pairs: merge the two ascending time lists,
-// comparing differentiae on common times until the first mismatch.
-constexpr uint32_t kGeneralPairRows = 512;   // grid rows of the general pairs kernel
-__global__ __launch_bounds__(256) void mrca_general_pairs_kernel(
+// General route, all ordered pairs.  An item keeps its site until it is
+// overwritten, and every annotation's items come from one history, so of a
+// pair with counters Ta >= Tb the retained items common to both are exactly
+// a's items older than Tb: a prefix of a's time order, at the same sites in
+// both.  The first mismatch is then the lowest time rank (in a's order)
+// among the differing sites, counted only if its time is below Tb, and the
+// item before it in a's order is the last agreeing one.
+//
+// The lowest rank among the set bits of a word is the least of eight table
+// entries, one per byte; the 2 KB of tables of a row serve all its columns.
+// A workgroup takes kPairTileRows rows and kPairTileCols columns (one per
+// thread) kPairColTiles times, and writes a pair into both its rows: the
+// row of the later annotation directly, the other one transposed through
+// LDS so that 16 lanes write 64 contiguous bytes (pairs of equal counters
+// are worked out once from each side).  Bound by LDS reads (ten a pair) and
+// the stores.  A merge of the two time lists, up to 128 dependent steps a
+// pair over global memory, took 1,148 us for 4,096 annotations of a hybrid
+// 64-site surface, this form 81 us.
+constexpr uint32_t kPairTileRows = 16, kPairTileCols = 256, kPairColTiles = 4;
+constexpr uint32_t kNoRank = 64;
+// words between columns of the transposed tile: 16 rows, then padding that
+// keeps the 16-byte alignment and spreads the banks
+constexpr uint32_t kPairStage = 20;
+
+__global__ __launch_bounds__(kPairTileCols) void mrca_general_pairs_kernel(
     uint32_t S, uint32_t diff_log2, uint32_t n, const uint32_t* __restrict__ counter,
     const uint32_t* __restrict__ surf, const uint32_t* __restrict__ times,
     const uint8_t* __restrict__ sites, const uint32_t* __restrict__ ws, uint32_t* __restrict__ lb,
     uint32_t* __restrict__ ub) {
     if (ws[kWsStatus] != kWsStatusMixed) return;
-    const uint32_t b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= n) return;
+    constexpr uint32_t R = kPairTileRows;
+    __shared__ __align__(16) uint8_t first[R][8][256];       // lowest rank of a byte's bits
+    __shared__ uint32_t t_of[R][64];                         // time of each rank
+    __shared__ uint64_t s_row[R];
+    __shared__ uint32_t T_row[R], T_col[kPairTileCols];
+    __shared__ __align__(16) uint32_t stage[2][kPairTileCols * kPairStage];
+    const uint32_t tid = threadIdx.x;
+    const uint32_t row0 = blockIdx.y * R;
     const uint32_t SW = (S << diff_log2) >> 5;
-    const uint64_t sb = surface64(surf, SW, b);
-    const uint64_t mask = diff_log2 ? 0xffull : 1ull;
-    const uint32_t* tb = times + (size_t)b * S;
-    const uint8_t* kb = sites + (size_t)b * S;
-    const uint32_t Tb = counter[b];
-    // rows a = blockIdx.y, blockIdx.y + gridDim.y, ...: a small grid, so that
-    // the shared-counter route, which skips this kernel, pays little for it
-    for (uint32_t a = blockIdx.y; a < n; a += gridDim.y) {
-        const uint64_t sa = surface64(surf, SW, a);
-        const uint32_t* ta = times + (size_t)a * S;
-        const uint8_t* ka = sites + (size_t)a * S;
-        uint32_t i = 0, k = 0;
-        bool have_last = false, mismatch = false;
-        uint32_t last = 0, tstar = 0;
-        while (i < S && k < S) {
-            const uint32_t x = ta[i], y = tb[k];
-            if (x == kEmpty || y == kEmpty) break;
-            if (x == y) {
-                if (((sa >> ((uint32_t)ka[i] << diff_log2)) & mask) !=
-                    ((sb >> ((uint32_t)kb[k] << diff_log2)) & mask)) {
-                    mismatch = true;
-                    tstar = x;
-                    break;
+
+    // the rows' tables, by way of rank by site and rank by nibble (in the
+    // memory of the stage, which is not in use yet)
+    uint8_t* rank_of = reinterpret_cast<uint8_t*>(stage[0]);            // [R][64]
+    uint8_t* nibble = rank_of + R * 64;                                  // [R][16][16]
+    for (uint32_t i = tid; i < R * 64; i += kPairTileCols) {
+        const uint32_t row = i >> 6, r = i & 63u, a = row0 + row;
+        uint32_t t = kEmpty;
+        if (r < S && a < n) {
+            t = times[(size_t)a * S + r];
+            rank_of[row * 64 + sites[(size_t)a * S + r]] = (uint8_t)r;
+        }
+        t_of[row][r] = t;
+    }
+    if (tid < R) {
+        const uint32_t a = row0 + tid;
+        s_row[tid] = a < n ? surface64(surf, SW, a) : 0ull;
+        T_row[tid] = a < n ? counter[a] : 0u;
+    }
+    __syncthreads();
+    {
+        const uint32_t row = tid >> 4, nib = tid & 15u;
+        uint32_t rk[4];
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k) {
+            const uint32_t site = (nib * 4 + k) >> diff_log2;
+            rk[k] = site < S && row0 + row < n ? rank_of[row * 64 + site] : kNoRank;
+        }
+        uint32_t val[16];
+        val[0] = kNoRank;
+#pragma unroll
+        for (uint32_t v = 1; v < 16; ++v) val[v] = min(val[v & (v - 1)], rk[__builtin_ctz(v)]);
+#pragma unroll
+        for (uint32_t v = 0; v < 16; ++v) nibble[tid * 16 + v] = (uint8_t)val[v];
+    }
+    __syncthreads();
+    for (uint32_t i = tid; i < R * 8 * 64; i += kPairTileCols) {
+        const uint32_t row = i >> 9, byte = (i >> 6) & 7u, q = i & 63u;   // values 4q .. 4q + 3
+        const uint8_t* lo = nibble + (row * 16 + byte * 2) * 16 + (q & 3u) * 4;
+        const uint32_t hi = nibble[(row * 16 + byte * 2 + 1) * 16 + (q >> 2)];
+        uint32_t w = 0;
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k) w |= min((uint32_t)lo[k], hi) << (8 * k);
+        reinterpret_cast<uint32_t*>(first)[i] = w;
+    }
+
+    for (uint32_t ct = 0; ct < kPairColTiles; ++ct) {
+        const uint32_t b0 = (blockIdx.x * kPairColTiles + ct) * kPairTileCols;
+        if (b0 >= n) break;
+        const uint32_t b = b0 + tid;
+        const uint64_t sb = b < n ? surface64(surf, SW, b) : 0ull;
+        // (a column past n is later than every row: it takes no part)
+        const uint32_t Tb = b < n ? counter[b] : kEmpty;
+        __syncthreads();          // tables built; the last tile's stage read
+        T_col[tid] = Tb;
+#pragma unroll
+        for (uint32_t g = 0; g < R; g += 4) {
+            uint32_t l4[4], u4[4];
+#pragma unroll
+            for (uint32_t q = 0; q < 4; ++q) {
+                const uint32_t row = g + q;
+                const uint64_t y = s_row[row] ^ sb;
+                const uint32_t y0 = (uint32_t)y, y1 = (uint32_t)(y >> 32);
+                uint32_t r = kNoRank;
+#pragma unroll
+                for (uint32_t k = 0; k < 4; ++k)
+                    r = min(r, (uint32_t)first[row][k][(y0 >> (8 * k)) & 0xffu]);
+                if (SW > 1) {
+#pragma unroll
+                    for (uint32_t k = 0; k < 4; ++k)
+                        r = min(r, (uint32_t)first[row][4 + k][(y1 >> (8 * k)) & 0xffu]);
                 }
-                have_last = true;
-                last = x;
-                ++i;
-                ++k;
-            } else if (x < y) {
-                ++i;
-            } else {
-                ++k;
+                u4[q] = r < kNoRank ? t_of[row][r] : kEmpty;
+                l4[q] = r - 1u < kNoRank - 1u ? t_of[row][r - 1u] + 1u : 0u;
+                const bool later = Tb <= T_row[row];
+                if (later && u4[q] >= Tb) {
+                    // no mismatch: the last of a's items older than Tb
+                    uint32_t f = 0;
+#pragma unroll
+                    for (uint32_t step = 32; step; step >>= 1)
+                        if (t_of[row][f + step - 1] < Tb) f += step;
+                    if (t_of[row][f] < Tb) ++f;
+                    u4[q] = Tb;
+                    l4[q] = f ? t_of[row][f - 1] + 1u : 0u;
+                }
+                if (later && row0 + row < n) {
+                    const size_t off = (size_t)(row0 + row) * n + b;
+                    lb[off] = l4[q];
+                    ub[off] = u4[q];
+                }
+            }
+            *reinterpret_cast<uint4*>(&stage[0][tid * kPairStage + g]) =
+                make_uint4(l4[0], l4[1], l4[2], l4[3]);
+            *reinterpret_cast<uint4*>(&stage[1][tid * kPairStage + g]) =
+                make_uint4(u4[0], u4[1], u4[2], u4[3]);
+        }
+        __syncthreads();
+        const uint32_t row = tid & (R - 1u), a = row0 + row;
+        for (uint32_t c = tid / R; c < kPairTileCols; c += kPairTileCols / R) {
+            if (a < n && T_col[c] < T_row[row]) {
+                const size_t off = (size_t)(b0 + c) * n + a;
+                lb[off] = stage[0][c * kPairStage + row];
+                ub[off] = stage[1][c * kPairStage + row];
             }
         }
-        const uint32_t Ta = counter[a];
-        const size_t off = (size_t)a * n + b;
-        ub[off] = mismatch ? tstar : (Ta < Tb ? Ta : Tb);
-        lb[off] = have_last ? last + 1u : 0u;
     }
 }
 
@@ -794,9 +889,10 @@ hipError_t launch_mrca(const Scheme& scm, uint32_t n, const uint32_t* counter,
                        dim3(256), 0, stream, n, diff_log2, ranked, ws, lb, ub);
     hipLaunchKernelGGL(mrca_layouts_kernel, dim3(n), dim3(64), 0, stream, scm, counter, ws,
                        times, sites, hint.rules);
-    const uint32_t rows = n < kGeneralPairRows ? n : kGeneralPairRows;
-    hipLaunchKernelGGL(mrca_general_pairs_kernel, dim3((n + 255) / 256, rows), dim3(256), 0,
-                       stream, S, diff_log2, n, counter, surf, times, sites, ws, lb, ub);
+    constexpr uint32_t cols = kPairTileCols * kPairColTiles;
+    hipLaunchKernelGGL(mrca_general_pairs_kernel,
+                       dim3((n + cols - 1) / cols, (n + kPairTileRows - 1) / kPairTileRows),
+                       dim3(kPairTileCols), 0, stream, S, diff_log2, n, counter, surf, times, sites, ws, lb, ub);
     return hipGetLastError();
 }
 
