@@ -176,18 +176,14 @@ int run_init(ga_run* r, const ga_config* cfg, uint8_t* base, uint32_t gens, hipS
     r->ring_hi = 0;
     r->gens = gens;
     r->T = 0;
+    r->cur = 0;
     r->horizon = hsga::horizon_gen_of(cfg->surface_kind, r->S, cfg->ingest_interval);
     r->apt = default_agents_per_thread(r->N);
-    // integer births with four agents per thread: small tiles, more
-    // workgroups in flight per CU -- 64 threads for synchronous runs on
-    // two-word surfaces, 128 for one-word ones and for asynchronous ticks
-    // (3 to 5 KB of records per tile, which measured fastest: the treatment
-    // pair's selection run 3-6 % faster at 128 than at 64, asynchronous
-    // ticks 1.4-2.2 %, the paper-scale run about 1 % slower); float births
-    // (VALU-bound) and the rest: 256 threads, which measured faster for them
-    const bool narrow = r->SW == 2 && cfg->async_activity == 0;
-    r->block = r->apt == 4 && birth_model(*cfg) != hsga::kBirthFloat ? (narrow ? 64u : 128u)
-                                                                        : 256u;
+    // 256 threads: a tile of 32 islands of 32 agents has 24 around it, and
+    // their work and the islands' is a wavefront's or two of the tile's four
+    // (paper-scale run: 59.2 us per generation at 64 threads, 51.0 at 128,
+    // 47.8 at 256, 51.5 at 512; asynchronous ticks 82.3, 77.9, 72.3, 75.1)
+    r->block = 256u;
     r->timing = false;
     hipError_t e = hsga::launch_founders(r->trait[0], r->counter[0], r->surf[0], r->A, r->SW,
                                          r->layout, r->S, cfg->fitness_model == GA_FOUNDER_TAG,
@@ -213,9 +209,82 @@ int set_run_layout(ga_run* r, uint32_t T) {
     return GA_OK;
 }
 
-hsga::StepParams step_params(const ga_run* r, uint32_t g, uint32_t tau0) {
+size_t shape_lds_bytes(uint32_t islands, uint32_t N, uint32_t SW, bool float_births,
+                       uint32_t block, uint32_t apt) {
+    const size_t TA = ((size_t)islands * N + 3) & ~(size_t)3;
+    const size_t b = ((2 + SW) * TA + 2 * (size_t)islands) * 4;
+    return float_births ? ((b + 15) & ~(size_t)15) + (size_t)block * apt * 8 : b;
+}
+
+namespace {
+
+// A tile of w x h islands of r's torus at its agents per thread.
+hsga::TileGeom make_tile(const ga_run* r, uint32_t w, uint32_t h, bool whole) {
+    hsga::TileGeom t{};
+    t.w = (uint16_t)w;
+    t.h = (uint16_t)h;
+    t.cols = (uint16_t)((r->cfg.grid_w + w - 1) / w);
+    t.rows = (uint16_t)((r->cfg.grid_h + h - 1) / h);
+    t.threads = (uint16_t)((w * h * (r->N / r->apt) + 63) / 64 * 64);
+    t.whole = whole ? 1 : 0;
+    t.n_magic = ((1u << 20) + r->N - 1) / r->N;
+    t.w_magic = ((1u << 20) + w - 1) / w;
+    t.isl_magic = ((1u << 20) + w * h - 1) / (w * h);
+    uint32_t shift;
+    hsga::column_magic(w + 2, &t.pw_magic, &shift);
+    t.pw_shift = (uint16_t)shift;
+    // a resident run draws for as many generations as one round of its
+    // threads holds
+    t.draws = (uint8_t)(whole ? std::min(std::max(t.threads / (2 * w * h), 1u), 8u)
+                              : hsga::kTileGens);
+    hsga::column_magic(whole ? w * h : t.cols, &t.cols_magic, &shift);
+    t.cols_shift = (uint16_t)shift;
+    return t;
+}
+
+size_t tile_lds(const ga_run* r, const hsga::TileGeom& t) {
+    return hsga::step_lds_bytes(t, r->N, r->SW, r->cfg.async_activity != 0,
+                                birth_model(r->cfg) == hsga::kBirthFloat, r->apt);
+}
+
+}  // namespace
+
+// The tile with the least work for the whole torus: every workgroup takes
+// the time of its wavefronts, full or not, and about a quarter of a birth
+// island's for each island around the tile (only those whose emigrant comes
+// in are worked out).  Squarer tiles have fewer islands around them (a
+// 4 x 2 tile 12 against 18 of an 8 x 1 tile); of equal ones the widest,
+// whose rows are the longest contiguous pieces.
+const hsga::TileGeom& run_tile(ga_run* r, uint32_t block) {
+    if (r->tile_block == block && r->tile_apt == r->apt) return r->tile;
+    const uint32_t W = r->cfg.grid_w, H = r->cfg.grid_h;
+    const uint32_t most = std::min(tile_islands(block, r->apt, r->N), kMaxTileIslands);
+    uint64_t best = ~0ull;
+    for (uint32_t h = 1; h <= std::min(H, most); ++h) {
+        const uint32_t fit = std::min(W, most / h);
+        // the same columns of tiles from the narrowest tile that gives them
+        const uint32_t cols = (W + fit - 1) / fit;
+        uint32_t w = (W + cols - 1) / cols;
+        hsga::TileGeom t = make_tile(r, w, h, false);
+        while (w > 1 && (2 * (w + h) > t.threads || tile_lds(r, t) > kMaxStepLds))
+            t = make_tile(r, --w, h, false);
+        if (2 * (w + h) > t.threads || tile_lds(r, t) > kMaxStepLds) break;
+        const uint64_t lanes = t.threads * r->apt + (uint64_t)(w + h) * r->N / 2;
+        const uint64_t cost = lanes * t.cols * t.rows;
+        if (cost < best) {
+            best = cost;
+            r->tile = t;
+        }
+    }
+    r->tile_block = block;
+    r->tile_apt = r->apt;
+    return r->tile;
+}
+
+hsga::StepParams step_params(const ga_run* r, uint32_t g, uint32_t gens, uint32_t cur,
+                             uint32_t tau0, const hsga::TileGeom& tile) {
     const ga_config& cfg = r->cfg;
-    const int src = g & 1, dst = (g + 1) & 1;
+    const uint32_t src = cur, dst = cur ^ 1u;
     hsga::StepParams p;
     p.in_trait = r->trait[src];
     p.in_counter = r->counter[src];
@@ -226,7 +295,8 @@ hsga::StepParams step_params(const ga_run* r, uint32_t g, uint32_t tau0) {
     p.ob_in = r->outbox[src];
     p.ob_out = r->outbox[dst];
     const uint32_t n = cfg.ingest_interval;
-    p.site = g % n == 0 && r->sites ? r->sites + (g / n - tau0) : nullptr;
+    p.sites = r->sites;
+    p.tau0 = tau0;
     p.diff_log2 = cfg.differentia_bits == 8 ? 3u : 0u;
     p.async_thr = cfg.async_activity;
     p.rules = r->rules;
@@ -241,6 +311,7 @@ hsga::StepParams step_params(const ga_run* r, uint32_t g, uint32_t tau0) {
     p.I = r->I;
     p.A = r->A;
     p.g = g;
+    p.gens = gens;
     p.k0 = (uint32_t)cfg.seed;
     p.k1 = (uint32_t)(cfg.seed >> 32);
     // founder tags: neutral, inherited unchanged
@@ -248,14 +319,12 @@ hsga::StepParams step_params(const ga_run* r, uint32_t g, uint32_t tau0) {
     p.mut_lo = cfg.mut_lo;
     p.mut_span = (uint32_t)((int64_t)cfg.mut_hi - cfg.mut_lo + 1);
     p.has_inbox = (cfg.migrants_per_island != 0 && g > 0) ? 1u : 0u;
-    p.tile_isl = tile_islands(r->block, r->apt, r->N);
-    p.div_magic = ((1u << 20) + r->N - 1) / r->N;
-    hsga::column_magic(cfg.grid_w, &p.w_magic, &p.w_shift);
+    p.tile = tile;
     p.tour = cfg.tournament_size > 1 ? cfg.tournament_size : 1u;
     p.del_thr = cfg.del_threshold;
     p.ben_thr = cfg.ben_threshold;
-    p.del_sigma = cfg.del_sigma;
-    p.ben_sigma = cfg.ben_sigma;
+    p.del_scale = -(double)cfg.del_sigma;
+    p.ben_scale = cfg.ben_sigma;
     return p;
 }
 
@@ -360,12 +429,28 @@ namespace {
 uint32_t resident_block(const ga_run* r) {
     if (!r->resident || r->cfg.async_activity || r->A > kResidentMaxAgents) return 0;
     const uint32_t block = ((r->A + r->apt - 1) / r->apt + 63) / 64 * 64;
-    const uint32_t tile_isl = tile_islands(block, r->apt, r->N);
-    if (block > 1024 || tile_isl < r->I || tile_isl > block) return 0;
-    if (hsga::step_lds_bytes(tile_isl, r->N, r->SW, birth_model(r->cfg) == hsga::kBirthFloat,
-                             block, r->apt) > kMaxStepLds)
+    const uint32_t islands = tile_islands(block, r->apt, r->N);
+    if (block > 1024 || islands < r->I || islands > block) return 0;
+    if (shape_lds_bytes(islands, r->N, r->SW, birth_model(r->cfg) == hsga::kBirthFloat, block,
+                        r->apt) > kMaxStepLds)
         return 0;
     return block;
+}
+
+// Launches of at most `per` generations each, n in all, from the run's
+// generation r->T + done on.
+int enqueue_steps(ga_run* r, const hsga::TileGeom& tile, uint32_t done, uint32_t n, uint32_t per,
+                  uint32_t tau0) {
+    const uint32_t model = birth_model(r->cfg);
+    const bool mig = r->cfg.migrants_per_island != 0;
+    for (uint32_t k = 0; k < n; k += per) {
+        const uint32_t gens = std::min(per, n - k);
+        const hsga::StepParams p = step_params(r, r->T + done + k, gens, r->cur, tau0, tile);
+        hipError_t e = hsga::launch_step(p, r->SW, model, mig, r->apt, r->stream);
+        if (e != hipSuccess) return hip_fail(e, "step launch");
+        r->cur ^= 1u;
+    }
+    return GA_OK;
 }
 
 int step_enqueue(ga_run* r, uint32_t n) {
@@ -374,11 +459,13 @@ int step_enqueue(ga_run* r, uint32_t n) {
                                      " is past the site rule's horizon " +
                                      std::to_string(r->horizon));
     const ga_config& cfg = r->cfg;
-    const uint32_t model = birth_model(cfg);
-    const bool mig = cfg.migrants_per_island != 0;
+    // without migration an island needs nothing of the others, so a tile's
+    // launch takes as many generations as a batch has
+    const uint32_t per = cfg.migrants_per_island == 0 && cfg.async_activity == 0
+                             ? r->gens : hsga::kTileGens;
     if (cfg.async_activity) {
-        // asynchronous ticks: one launch per tick; each birth finds its site
-        // from its parent's counter in the rule's tables
+        // asynchronous ticks: each birth finds its site from its parent's
+        // counter in the rule's tables
         ga_run::Span span{nullptr, nullptr, n};
         if (r->timing) {
             span.start = take_event(r);
@@ -387,25 +474,22 @@ int step_enqueue(ga_run* r, uint32_t n) {
             hipError_t e = hipEventRecord(span.start, r->stream);
             if (e != hipSuccess) return hip_fail(e, "hipEventRecord");
         }
-        for (uint32_t k = 0; k < n; ++k) {
-            if ((k & (hsga::kSiteRing / 2 - 1)) == 0) {
-                // the ring takes the ingests the next half ring of ticks can
-                // reach (a parent's counter is at most the tick)
-                const uint32_t last = (uint32_t)std::min<uint64_t>(
-                    (uint64_t)r->T + k + hsga::kSiteRing / 2, (uint64_t)r->T + n);
-                const uint32_t hi = hsga::ingests_of(last, cfg.ingest_interval);
-                if (hi > r->ring_hi) {
-                    const uint32_t lo = std::max(r->ring_hi, hi > hsga::kSiteRing
-                                                                 ? hi - hsga::kSiteRing : 0u);
-                    hipError_t e = hsga::launch_fill_site_ring(r->rules, cfg.surface_kind, r->S,
-                                                               r->ring, lo, hi - lo, r->stream);
-                    if (e != hipSuccess) return hip_fail(e, "site ring launch");
-                    r->ring_hi = hi;
-                }
+        for (uint32_t k = 0; k < n;) {
+            // the ring takes the ingests the next half ring of ticks can
+            // reach (a parent's counter is at most the tick)
+            const uint32_t part = std::min(n - k, hsga::kSiteRing / 2);
+            const uint32_t hi = hsga::ingests_of(r->T + k + part, cfg.ingest_interval);
+            if (hi > r->ring_hi) {
+                const uint32_t lo = std::max(r->ring_hi,
+                                             hi > hsga::kSiteRing ? hi - hsga::kSiteRing : 0u);
+                hipError_t e = hsga::launch_fill_site_ring(r->rules, cfg.surface_kind, r->S,
+                                                           r->ring, lo, hi - lo, r->stream);
+                if (e != hipSuccess) return hip_fail(e, "site ring launch");
+                r->ring_hi = hi;
             }
-            const hsga::StepParams p = step_params(r, r->T + k, 0);
-            hipError_t e = hsga::launch_step(p, r->SW, model, mig, r->apt, r->block, r->stream);
-            if (e != hipSuccess) return hip_fail(e, "step launch");
+            const int rc = enqueue_steps(r, run_tile(r, r->block), k, part, per, 0);
+            if (rc != GA_OK) return rc;
+            k += part;
         }
         if (r->timing) {
             hipError_t e = hipEventRecord(span.stop, r->stream);
@@ -432,21 +516,12 @@ int step_enqueue(ga_run* r, uint32_t n) {
             e = hipEventRecord(span.start, r->stream);
             if (e != hipSuccess) return hip_fail(e, "hipEventRecord");
         }
-        const uint32_t rb = resident_block(r);
-        if (rb) {
-            // the whole batch in one workgroup
-            hsga::StepParams p = step_params(r, r->T, tau0);
-            p.tile_isl = tile_islands(rb, r->apt, r->N);
-            e = hsga::launch_resident_step(p, G, r->sites, tau0, r->SW, model, mig, r->apt, rb,
-                                           r->stream);
-            if (e != hipSuccess) return hip_fail(e, "resident step launch");
-        } else {
-            for (uint32_t k = 0; k < G; ++k) {
-                const hsga::StepParams p = step_params(r, r->T + k, tau0);
-                e = hsga::launch_step(p, r->SW, model, mig, r->apt, r->block, r->stream);
-                if (e != hipSuccess) return hip_fail(e, "step launch");
-            }
-        }
+        // a run that fits one workgroup takes the whole batch in it
+        const int rc = resident_block(r)
+                           ? enqueue_steps(r, make_tile(r, cfg.grid_w, cfg.grid_h, true), 0, G, G,
+                                           tau0)
+                           : enqueue_steps(r, run_tile(r, r->block), 0, G, per, tau0);
+        if (rc != GA_OK) return rc;
         if (r->timing) {
             e = hipEventRecord(span.stop, r->stream);
             if (e != hipSuccess) return hip_fail(e, "hipEventRecord");
@@ -480,7 +555,7 @@ int ga_read_agents(ga_run* r, uint32_t first, uint32_t count, uint32_t* trait, u
     if (!r) return fail(GA_EINVAL, "run is NULL");
     if ((uint64_t)first + count > r->A) return fail(GA_EINVAL, "agent range out of bounds");
     if (count == 0) return GA_OK;
-    const int cur = r->T & 1;
+    const uint32_t cur = r->cur;
     hipError_t e = hipStreamSynchronize(r->stream);
     if (e != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
     if (trait) {
@@ -519,7 +594,7 @@ int ga_read_outbox(ga_run* r, uint32_t first, uint32_t count, uint32_t* dir, uin
     const uint32_t words = async ? hsga::kOutboxWords : hsga::kSyncOutboxWords;
     const uint32_t surf0 = async ? 3 : 2;
     std::vector<uint32_t> entries((size_t)count * words);
-    e = hipMemcpy(entries.data(), r->outbox[r->T & 1] + (size_t)first * words,
+    e = hipMemcpy(entries.data(), r->outbox[r->cur] + (size_t)first * words,
                   entries.size() * 4, hipMemcpyDeviceToHost);
     if (e != hipSuccess) return hip_fail(e, "hipMemcpy outbox");
     for (uint32_t k = 0; k < count; ++k) {
@@ -551,7 +626,7 @@ int ga_sample(ga_run* r, uint32_t n, uint32_t* dev_idx, uint32_t* dev_counter,
     if (!r || !n_taken) return fail(GA_EINVAL, "NULL argument");
     if (n == 0 || !dev_idx || !dev_counter || !dev_surface_words)
         return fail(GA_EINVAL, "empty sample or NULL buffer");
-    const int cur = r->T & 1;
+    const uint32_t cur = r->cur;
     hipError_t e = hsga::launch_sample(r->counter[cur], r->surf[cur], r->A, r->SW, n, r->T,
                                        (uint32_t)r->cfg.seed, (uint32_t)(r->cfg.seed >> 32),
                                        dev_idx, dev_counter, dev_surface_words, r->stream);
@@ -582,7 +657,7 @@ int ga_export_state(ga_run* r, void* host, size_t bytes) {
     w[3] = r->T;
     std::memcpy(w + kStateHeaderWords, &r->cfg, sizeof(ga_config));
     uint32_t* at = w + kStateHeaderWords + sizeof(ga_config) / 4;
-    const int cur = r->T & 1;
+    const uint32_t cur = r->cur;
     const size_t A = r->A;
     // a synchronous run keeps no counter plane: every counter is T
     const struct { const uint32_t* src; size_t words; } planes[] = {
@@ -644,7 +719,7 @@ int ga_import_state(ga_run* r, const void* host, size_t bytes) {
         }
     hipError_t e = hipStreamSynchronize(r->stream);
     if (e != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
-    const int cur = T & 1;
+    const uint32_t cur = 0;
     const struct { uint32_t* dst; const uint32_t* src; size_t words; } planes[] = {
         {r->trait[cur], trait, A}, {r->counter[cur], counter, A}, {r->surf[cur], surf, r->SW * A},
         {r->outbox[cur], ob, outbox ? (size_t)r->I * E : 0}};
@@ -661,6 +736,7 @@ int ga_import_state(ga_run* r, const void* host, size_t bytes) {
     e = hipStreamSynchronize(r->stream);
     if (e != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
     r->T = T;
+    r->cur = cur;
     r->broken = false;
     return GA_OK;
 }
@@ -929,8 +1005,8 @@ int ga_set_launch_shape(ga_run* r, uint32_t block_threads, uint32_t agents_per_t
         return fail(GA_EINVAL, "block_threads must be a multiple of 64 in 64..1024");
     if ((apt != 1 && apt != 2 && apt != 4) || r->N % apt)
         return fail(GA_EINVAL, "agents_per_thread must be 1, 2 or 4 and divide pop_per_island");
-    if (hsga::step_lds_bytes(tile_islands(block, apt, r->N), r->N, r->SW,
-                             birth_model(r->cfg) == hsga::kBirthFloat, block, apt) > kMaxStepLds)
+    if (shape_lds_bytes(tile_islands(block, apt, r->N), r->N, r->SW,
+                        birth_model(r->cfg) == hsga::kBirthFloat, block, apt) > kMaxStepLds)
         return fail(GA_EINVAL, "tile needs more than 64 KiB of LDS");
     r->block = block;
     r->apt = apt;

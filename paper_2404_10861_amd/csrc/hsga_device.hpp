@@ -106,12 +106,37 @@ __constant__ double kHalfNormalSeries[31] = {
     -1.0 / 2.0, 1.0,
 };
 
-// The draw for an angle word of a known case: SIN for w_angle >= 2^31 (the
-// sine series), else the cosine series.
-template <bool SIN>
-__device__ __forceinline__ double half_normal_case(uint32_t w_radius, uint32_t w_angle) {
+// c x + k with k in scalar registers.  Written as the instruction: the
+// compiler takes the accumulating form instead, which needs k copied into
+// vector registers first (two moves for each of 20 coefficients, a quarter
+// more instructions per draw).
+__device__ __forceinline__ double series_step(double c, double x, double k) {
+    double r;
+    asm("v_fma_f64 %0, %1, %2, %3" : "=v"(r) : "v"(c), "v"(x), "s"(k));
+    return r;
+}
+
+// The coefficients, through an opaque pointer, so that a draw loads them
+// itself: hoisted out of a large kernel's rounds they would not fit the
+// scalar registers.
+typedef const __attribute__((address_space(4))) double* HalfNormalCoefficients;
+
+__device__ __forceinline__ HalfNormalCoefficients half_normal_coefficients() {
+    HalfNormalCoefficients K = (HalfNormalCoefficients)kHalfNormalSeries;
+    asm volatile("" : "+s"(K));
+    return K;
+}
+
+// sqrt(-2 ln U1).  1/sqrt q starts from a cubic instead of the
+// definition's 9/8 - 3q/16 and so takes three Newton steps where it takes
+// six: 12 instructions for 19, with the same result to the last bit for each
+// of the 2^32 radius words (compared one by one on this chip: sqrt q's
+// correction step squares what is left of the error, a rounding in either
+// case).  1/(m+1) keeps the definition's five steps from 1/2: they stop
+// 1e-22 off at the ends, which the last rounding does see for a few words.
+__device__ __forceinline__ double half_normal_radius(HalfNormalCoefficients K,
+                                                     uint32_t w_radius) {
 #pragma clang fp contract(off)
-    const double* K = kHalfNormalSeries;
     // ln U1.  v = 2 w_radius + 1 < 2^33 is exact in binary64; its exponent
     // is floor(log2 v), and setting the exponent to 0 gives v 2^-e exactly
     const double vd = __builtin_fma(2.0, (double)w_radius, 1.0);
@@ -130,7 +155,7 @@ __device__ __forceinline__ double half_normal_case(uint32_t w_radius, uint32_t w
     const double z = sv * sv;
     double p = K[0];
 #pragma unroll
-    for (int k = 1; k < 11; ++k) p = __builtin_fma(p, z, K[k]);
+    for (int k = 1; k < 11; ++k) p = series_step(p, z, K[k]);
     const double ln_u = __builtin_fma((double)e - 33.0, 0.6931471805599453, (sv + sv) * p);
     // sqrt(-2 ln U1)
     const double y = -2.0 * ln_u;
@@ -141,41 +166,48 @@ __device__ __forceinline__ double half_normal_case(uint32_t w_radius, uint32_t w
     const double q =
         __longlong_as_double((long long)((yb & kMantissa) | ((uint64_t)(1023 + (ex & 1)) << 52)));
     const double h = 0.5 * q;
-    double rs = __builtin_fma(-0.1875, q, 1.125);
+    double rs = __builtin_fma(
+        __builtin_fma(__builtin_fma(-0.01905041, q, 0.1946857), q, -0.73886303), q, 1.5561871);
 #pragma unroll
-    for (int i = 0; i < 6; ++i) rs = __builtin_fma(rs, __builtin_fma(-h, rs * rs, 0.5), rs);
+    for (int i = 0; i < 3; ++i) rs = __builtin_fma(rs, __builtin_fma(-h, rs * rs, 0.5), rs);
     double sq = q * rs;
     sq = __builtin_fma(__builtin_fma(-sq, sq, q), 0.5 * rs, sq);
-    const double radius = __builtin_ldexp(sq, kq);                          // exact scaling
-    // cos(pi/2 U2).  2 w_angle + 1, or 2^33 - (2 w_angle + 1) in the sine
-    // case, is an exact binary64 integer; the 2^-33 is folded into pi/2
-    // (an exact power-of-two scaling of it, so the product rounds the same)
+    return __builtin_ldexp(sq, kq);                                         // exact scaling
+}
+
+// cos(pi/2 U2) for an angle word of a known case: SIN for w_angle >= 2^31
+// (the sine series), else the cosine series.  2 w_angle + 1, or 2^33 -
+// (2 w_angle + 1) in the sine case, is an exact binary64 integer; the 2^-33
+// is folded into pi/2 (an exact power-of-two scaling of it, so the product
+// rounds the same).
+template <bool SIN>
+__device__ __forceinline__ double half_normal_angle(HalfNormalCoefficients K, uint32_t w_angle) {
+#pragma clang fp contract(off)
     const double wad = (double)w_angle;
     const double va = SIN ? __builtin_fma(-2.0, wad, 8589934591.0) : __builtin_fma(2.0, wad, 1.0);
     const double x = va * (1.5707963267948966 * 0x1p-33);
     const double x2 = x * x;
-    double c;
-    if constexpr (SIN) {
-        c = K[11];
+    constexpr int first = SIN ? 11 : 21;
+    double c = K[first];
 #pragma unroll
-        for (int k = 12; k < 21; ++k) c = __builtin_fma(c, x2, K[k]);
-        c = x * c;
-    } else {
-        c = K[21];
-#pragma unroll
-        for (int k = 22; k < 31; ++k) c = __builtin_fma(c, x2, K[k]);
-    }
-    return radius * c;
+    for (int k = first + 1; k < first + 10; ++k) c = series_step(c, x2, K[k]);
+    return SIN ? x * c : c;
+}
+
+// The draw.
+__device__ __forceinline__ double half_normal(uint32_t w_radius, uint32_t w_angle) {
+    const HalfNormalCoefficients K = half_normal_coefficients();
+    const double radius = half_normal_radius(K, w_radius);
+    return radius * (w_angle >= 0x80000000u ? half_normal_angle<true>(K, w_angle)
+                                            : half_normal_angle<false>(K, w_angle));
 }
 
 // The fitness after a draw: f - del_sigma |Z| (deleterious) or
 // f + ben_sigma |Z|, in binary64, rounded to binary32.  Written as one
-// product and one sum with the sign folded into the factor: negation is
+// product and one sum with the sign folded into the scale s: negation is
 // exact and rounding is symmetric, so f + (-s) z rounds as f - s z.
-__device__ __forceinline__ float apply_half_normal(float f, bool deleterious, float del_sigma,
-                                                   float ben_sigma, double z) {
+__device__ __forceinline__ float apply_half_normal(float f, double s, double z) {
 #pragma clang fp contract(off)
-    const double s = deleterious ? -(double)del_sigma : (double)ben_sigma;
     return (float)((double)f + s * z);
 }
 

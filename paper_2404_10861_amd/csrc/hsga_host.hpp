@@ -28,9 +28,12 @@ struct ga_run {
                          // last kSiteRing of them)
     uint32_t gens;       // site schedule capacity
     uint32_t T;          // generations (ticks, when asynchronous) enqueued
+    uint32_t cur;        // the ping-pong buffers that hold generation T
     uint64_t horizon;
     uint32_t apt;        // agents per thread (1, 2, 4; divides N)
     uint32_t block;      // workgroup threads
+    hsga::TileGeom tile; // of launches at shape (tile_block, apt); tile_block 0: not chosen yet
+    uint32_t tile_block = 0, tile_apt = 0;
     bool timing;
     bool pooled = false; // a slot of a pool (its generation targets live there)
     bool resident = true;  // a synchronous run that fits one workgroup steps resident
@@ -49,6 +52,9 @@ constexpr size_t kMaxStepLds = 65536;
 // torus): past this many agents the generation's births on one CU take
 // longer than a launch over many CUs.
 constexpr uint32_t kResidentMaxAgents = 4096;
+
+// Islands of a tile (more only if it is the whole torus).
+constexpr uint32_t kMaxTileIslands = 256;
 
 int fail(int status, const std::string& msg);
 int hip_fail(hipError_t e, const char* what);
@@ -85,15 +91,26 @@ int validate(const ga_config* in, ga_config* out);
 // carve(...).total bytes) and enqueue the founders.
 int run_init(ga_run* r, const ga_config* cfg, uint8_t* base, uint32_t gens, hipStream_t stream);
 
+// Islands that a workgroup's threads hold.
 inline uint32_t tile_islands(uint32_t block, uint32_t apt, uint32_t N) { return block * apt / N; }
+
+// LDS bytes by which a launch shape is accepted: the records of its islands
+// with a counter each, two draw words per island, the float births' queues.
+// A tile is chosen to fit whatever this accepts.
+size_t shape_lds_bytes(uint32_t islands, uint32_t N, uint32_t SW, bool float_births,
+                       uint32_t block, uint32_t apt);
+
+// The run's tile for launches of `block` threads.
+const hsga::TileGeom& run_tile(ga_run* r, uint32_t block);
 
 // Enqueue the run's layout after the ingests of generation (tick) count T
 // (closed form of the site rule, written by a kernel).
 int set_run_layout(ga_run* r, uint32_t T);
 
-// Parameters of generation g of a run whose current site schedule starts
-// at ingest tau0.
-hsga::StepParams step_params(const ga_run* r, uint32_t g, uint32_t tau0);
+// Parameters of generations g .. g + gens - 1 of a run from its buffers cur
+// into the others; its current site schedule starts at ingest tau0.
+hsga::StepParams step_params(const ga_run* r, uint32_t g, uint32_t gens, uint32_t cur,
+                             uint32_t tau0, const hsga::TileGeom& tile);
 
 // hsga::BirthModel of a configuration.
 uint32_t birth_model(const ga_config& cfg);

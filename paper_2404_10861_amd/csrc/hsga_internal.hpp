@@ -26,6 +26,26 @@ enum BirthModel : uint32_t {
     kBirthFloat = 2,           // binary32 fitness, tournament of `tour`, half-normal mutations
 };
 
+// Generations of one launch of a run that is more than one tile: the
+// emigrants of the islands around a tile reach one generation ahead.
+constexpr uint32_t kTileGens = 2;
+
+// A workgroup's tile of whole islands: w x h islands of the torus in
+// cols x rows tiles (the last ones of a row or column may be ragged), or
+// the whole torus (whole).
+struct TileGeom {
+    uint16_t w, h, cols, rows;
+    uint16_t threads;                  // of its workgroup
+    uint8_t whole;
+    uint8_t draws;                     // generations whose island draws are held at once
+    uint16_t pw_shift, cols_shift;
+    uint32_t n_magic;                  // ceil(2^20 / N): la / N == (la * n_magic) >> 20, la < 4096
+    uint32_t w_magic;                  // the same for w, below 1,024 islands
+    uint32_t isl_magic;                // the same for w h <= 256, below 2,048
+    uint32_t pw_magic;                 // e / (w + 2) by multiplication (column_magic)
+    uint32_t cols_magic;               // tile / cols (the whole torus: draw / its islands)
+};
+
 struct StepParams {
     const uint32_t* in_trait;
     const uint32_t* in_counter;
@@ -35,17 +55,16 @@ struct StepParams {
     uint32_t* out_surf;
     const uint32_t* ob_in;     // I entries of 8 words (read at generation g)
     uint32_t* ob_out;          // I entries of 8 words (written for g + 1)
-    const uint32_t* site;      // this generation's surface site; nullptr: no deposit
+    const uint32_t* sites;     // synchronous: the launch batch's schedule from ingest tau0
+    uint32_t tau0;
     uint32_t W, H, N, I, A;
-    uint32_t g;
+    uint32_t g, gens;          // generations g .. g + gens - 1
     uint32_t k0, k1;           // Philox key (seed)
     uint32_t mut_thr;
     int32_t mut_lo;
     uint32_t mut_span;         // mut_hi - mut_lo + 1
     uint32_t has_inbox;        // outboxes of generation g exist
-    uint32_t tile_isl;         // islands per workgroup tile
-    uint32_t div_magic;        // ceil(2^20 / N): la / N == (la * div_magic) >> 20 for la < 4096
-    uint32_t w_magic, w_shift; // isl / W by multiplication (column_magic)
+    TileGeom tile;
     uint32_t diff_log2;        // log2 of the differentia width: 0 (bit) or 3 (byte)
     uint32_t async_thr;        // asynchronous ticks: island activity threshold; 0: synchronous
     const RuleTable* rules;    // asynchronous ticks: the surface's site rule tables
@@ -56,22 +75,21 @@ struct StepParams {
     uint32_t interval;         // asynchronous ticks: the ingest interval
     uint32_t tour;             // float model: tournament draws, 1..5
     uint32_t del_thr, ben_thr; // float model: mutation class thresholds
-    float del_sigma, ben_sigma;
+    double del_scale, ben_scale;   // float model: -del_sigma and ben_sigma
 };
 
 // One run of a batched launch: a device-resident table entry, written by the
-// host before each batch.  The step of generation T0 + k uses ping-pong
-// buffers (T0 + k) & 1 -> (T0 + k + 1) & 1 and site sites[k]; a run with
-// k >= gens sits the launch out.
+// host before each batch.  Launch k steps generations T0 + k kTileGens on,
+// from buffers k & 1 into the others; a run that has done its gens sits the
+// launch out.
 struct BatchRun {
-    uint32_t* trait[2];
-    uint32_t* counter[2];
+    uint32_t* trait[2];        // [0]: the run's current population
     uint32_t* surf[2];
     uint32_t* outbox[2];
     uint32_t* sites;           // this batch's site schedule
     uint32_t* layout;          // the run's layout (S words)
     const RuleTable* rules;    // the surface's site rule tables (device)
-    uint32_t W, H, N, I, A;
+    uint32_t W, H, N;
     uint32_t T0, gens;
     uint32_t k0, k1;
     uint32_t mut_thr;
@@ -84,9 +102,9 @@ struct BatchRun {
     float del_sigma, ben_sigma;
     uint32_t interval;         // one deposit every `interval` generations
     uint32_t diff_log2;        // 0: one-bit differentiae, 3: bytes
-    uint32_t tile_isl, div_magic;
-    uint32_t w_magic, w_shift;
+    TileGeom tile;
 };
+static_assert(sizeof(BatchRun) == 192, "a pool's overhead holds one entry per run");
 
 // Division of any 32-bit n by a fixed d >= 1 as a multiply-high and
 // shifts (the round-down method with an add indicator, Granlund and
@@ -104,12 +122,10 @@ inline void column_magic(uint32_t d, uint32_t* magic, uint32_t* shift) {
 
 constexpr uint32_t kMaxBatchRuns = 256;
 
-// LDS bytes of one step workgroup.
-size_t step_lds_bytes(uint32_t tile_isl, uint32_t N, uint32_t SW);
-// ... and with the float births' draw queues (8 bytes per agent slot of the
-// workgroup, block_threads * apt).
-size_t step_lds_bytes(uint32_t tile_isl, uint32_t N, uint32_t SW, bool float_births,
-                      uint32_t block_threads, uint32_t apt);
+// LDS bytes of one step workgroup (the float births' draw queues, 8 bytes
+// per agent slot of the workgroup, among them).
+size_t step_lds_bytes(const TileGeom& tg, uint32_t N, uint32_t SW, bool async,
+                      bool float_births, uint32_t apt);
 
 // tags: founders' trait words are random 16-bit founder tags (key k0, k1);
 // counter may be nullptr (a synchronous run keeps no counter plane).
@@ -124,8 +140,6 @@ hipError_t launch_founders(uint32_t* trait, uint32_t* counter, uint32_t* surf, u
 hipError_t launch_run_sites(const RuleTable* rules, uint32_t kind, uint32_t S, uint32_t* sites,
                             uint32_t* layout, uint32_t tau0, uint32_t count, hipStream_t stream);
 
-// agents_per_thread (1, 2 or 4) must divide N; tile_isl * N <= block_threads *
-// agents_per_thread.
 // Asynchronous runs keep the sites of their most recent kSiteRing ingests
 // in a ring (filled from the rule's tables) for the common case, a parent
 // counter near the tick; older counters take the tables directly.
@@ -138,22 +152,18 @@ hipError_t launch_fill_site_ring(const RuleTable* rules, uint32_t kind, uint32_t
 hipError_t launch_set_layout(uint32_t* layout, const uint32_t* words, uint32_t S,
                              hipStream_t stream);
 
+// Generations p.g .. p.g + p.gens - 1 (at most kTileGens with migration or
+// asynchronous ticks, any number in a tile that is the whole torus: the
+// resident form, one workgroup, synchronous runs only).  agents_per_thread
+// (1, 2 or 4) must divide N; the tile's agents fit its threads.
 hipError_t launch_step(const StepParams& p, uint32_t SW, uint32_t birth_model, bool migration,
-                       uint32_t agents_per_thread, uint32_t block_threads, hipStream_t stream);
-// The resident form: gens generations of a synchronous run whose torus is
-// one tile (p.tile_isl >= p.I at block_threads), in one workgroup, from
-// generation p.g on; sites holds the launch batch's schedule from ingest
-// tau0 (launch_run_sites).
-hipError_t launch_resident_step(const StepParams& p, uint32_t gens, const uint32_t* sites,
-                                uint32_t tau0, uint32_t SW, uint32_t birth_model, bool migration,
-                                uint32_t agents_per_thread, uint32_t block_threads,
-                                hipStream_t stream);
+                       uint32_t agents_per_thread, hipStream_t stream);
 
 // Batched forms.  Every run's sites for its generations T0 .. T0 + gens - 1 and its layout
 // after them (launch_run_sites per run); max_gens bounds every run's gens.
 hipError_t launch_batch_sites(const BatchRun* runs, uint32_t nruns, uint32_t max_gens,
                               hipStream_t stream);
-// One generation of every run: total_tiles workgroups, workgroup b on XCD
+// Launch k, kTileGens generations of every run: total_tiles workgroups, workgroup b on XCD
 // b mod kXcds as its (b / kXcds)-th.  xcd_tab (2 * kXcds * nruns words):
 // for each XCD x, pre[x][i] = the offset of run i's chunk among x's
 // workgroups (ascending in i, pre[x][0] = 0); then for each XCD x,

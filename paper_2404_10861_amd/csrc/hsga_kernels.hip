@@ -131,32 +131,42 @@ hipError_t launch_set_layout(uint32_t* layout, const uint32_t* words, uint32_t S
 }
 
 // ---------------------------------------------------------------------------
-// One generation, (P_g, O_g) -> (P_{g+1}, O_{g+1}) (Methods, Asynchronous
-// Island-model Genetic Algorithm).
+// Generations of the step, (P_g, O_g) -> (P_{g+K}, O_{g+K}) (Methods,
+// Asynchronous Island-model Genetic Algorithm), K = p.gens in one launch.
 //
-// One workgroup per tile of whole islands; the tile's population is staged
-// in LDS as structure-of-arrays planes.
+// One workgroup per tile of tile_w x tile_h whole islands; the tile's
+// population is staged in LDS as structure-of-arrays planes and stays there
+// for the launch's K generations.  A generation needs nothing of the
+// neighbouring islands but the emigrants that they posted in the generation
+// before, so a second generation needs, of each island around the tile, one
+// birth: the emigrant's.  Only the islands whose emigrant comes the tile's
+// way (a quarter of them) work it out, from P_g and O_g in memory; the
+// same draws give the same child in the island's own tile.  Planes and
+// outboxes are then read and written once for two generations, where one
+// generation per launch was bound by that traffic.  Paper-scale run (16.8 M
+// agents, two-word surfaces): 70.5 us per generation with one a launch (5.9
+// TB/s, 415 VALU instructions per wavefront), 45.8 us with two (357 per
+// generation, 79 % of VALU issue; a float trial's generation 98 %).
 //  1. Each thread issues one 16-byte (APT = 4) non-temporal load per plane
 //     for its APT consecutive agents: traits and surface words, counters
 //     only for asynchronous ticks (in a synchronous run every counter is the
-//     generation number).  In the same round thread t issues the loads of
-//     island t's four neighbour outbox entries (direction word and record
-//     together), the island pass draws the immigration and emigration
-//     Philox blocks, and, while the loads are in flight, each thread draws
+//     generation number).  In the same round the threads issue the loads of
+//     the outbox entries of the tile's islands and of those around it, the
+//     islands' draws for two generations are made, one lane per draw, the
+//     emigrants of the islands around are worked out, and each thread draws
 //     the Philox blocks of its births.
-//  2. Records go to LDS; after a barrier, the thread of each island copies
-//     the neighbours' emigrants addressed to it over the drawn slots,
-//     north, south, west, east (a later one wins).
-//  3. After a second barrier each thread gives birth to its APT agents: a
-//     tournament of two over the island's LDS traits, the parent record
-//     copied from LDS, trait mutation, counter + 1 and the differentia bit
-//     written at this generation's site.  After the loop the thread holding
-//     the island's emigrant posts its copy to the outbox for g + 1.
-//     Children leave with one 16-byte store per plane (the counter plane
-//     only for asynchronous ticks).
-// Immigration slots: bits 6d .. 6d+5 = slot for direction d.  Emigration
+//  2. Records and entries go to LDS; after a barrier, the thread of each
+//     island copies the neighbours' emigrants addressed to it over the
+//     drawn slots, north, south, west, east (a later one wins).
+//  3. Each thread gives birth to its APT agents: a tournament of two over
+//     the island's LDS traits, the parent record copied from LDS, trait
+//     mutation, counter + 1 and the differentia bit written at this
+//     generation's site.  The children replace the staged records and the
+//     thread holding the island's emigrant posts its copy in LDS, or, after
+//     the last generation, the children leave with one 16-byte store per
+//     plane and the emigrant goes to the outbox.
+// Immigration word: bits 6d .. 6d+5 = slot for direction d.  Emigration
 // word: bits 0..7 = slot, 8..10 = direction (4: none, an idle island).
-// Plan word (asynchronous ticks): bit 31 = the island is active.
 template <int APT>
 struct Lanes {
     uint32_t v[APT];
@@ -165,10 +175,13 @@ struct Lanes {
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
-// Population planes stream through once per generation: global accesses
+// Population planes stream through once per launch: global accesses
 // carry the non-temporal hint.  LDS accesses are APT-word aligned.
+// at: the first agent (a plane's byte offsets fit 32 bits).
 template <int APT>
-__device__ __forceinline__ Lanes<APT> load_lanes(const uint32_t* __restrict__ src) {
+__device__ __forceinline__ Lanes<APT> load_lanes(const uint32_t* __restrict__ plane, uint32_t at) {
+    const uint32_t* src = reinterpret_cast<const uint32_t*>(
+        reinterpret_cast<const char*>(plane) + (uint32_t)(at * 4u));
     Lanes<APT> r;
     if constexpr (APT == 4) {
         const u32x4 x = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(src));
@@ -183,7 +196,10 @@ __device__ __forceinline__ Lanes<APT> load_lanes(const uint32_t* __restrict__ sr
 }
 
 template <int APT>
-__device__ __forceinline__ void store_lanes(uint32_t* __restrict__ dst, const Lanes<APT>& r) {
+__device__ __forceinline__ void store_lanes(uint32_t* __restrict__ plane, uint32_t at,
+                                            const Lanes<APT>& r) {
+    uint32_t* dst = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(plane) +
+                                                (uint32_t)(at * 4u));
     if constexpr (APT == 4) {
         u32x4 x = {r.v[0], r.v[1], r.v[2], r.v[3]};
         __builtin_nontemporal_store(x, reinterpret_cast<u32x4*>(dst));
@@ -207,13 +223,10 @@ __device__ __forceinline__ void lds_store_lanes(uint32_t* dst, const Lanes<APT>&
     }
 }
 
-// Column of island isl on a torus W wide: isl mod W, the quotient by the
-// run's multiplier (column_magic).
-__device__ __forceinline__ uint32_t column_of(uint32_t isl, uint32_t W, uint32_t magic,
-                                              uint32_t shift) {
-    const uint32_t t = __umulhi(isl, magic);
-    const uint32_t q = (t + ((isl - t) >> (shift & 0xffu))) >> (shift >> 8);
-    return isl - q * W;
+// n / d by d's multiplier (column_magic).
+__device__ __forceinline__ uint32_t quotient_of(uint32_t n, uint32_t magic, uint32_t shift) {
+    const uint32_t t = __umulhi(n, magic);
+    return (t + ((n - t) >> (shift & 0xffu))) >> (shift >> 8);
 }
 
 // Island index of a neighbour: 0 north, 1 south, 2 west, 3 east (torus).
@@ -225,279 +238,480 @@ __device__ __forceinline__ uint32_t neighbour_of(uint32_t isl, uint32_t x, uint3
     return x + 1 < W ? isl + 1 : isl + 1 - W;
 }
 
-// Set bits of a wave mask on lanes below this one.
-__device__ __forceinline__ uint32_t lanes_below(uint64_t m) {
-    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+// base + the set bits of a wave mask on lanes below this one.
+__device__ __forceinline__ uint32_t lanes_below(uint64_t m, uint32_t base = 0u) {
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                     __builtin_amdgcn_mbcnt_lo((uint32_t)m, base));
+}
+
+// This wavefront's LDS accesses so far come before its later ones.
+__device__ __forceinline__ void wave_order() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 }
 
 extern __shared__ __attribute__((aligned(16))) uint32_t g_step_lds[];
 
-// The Philox blocks of a thread's APT births (and the second blocks of
+// The LDS of a tile of RI islands, in words: trait, counter (asynchronous
+// ticks) and surface planes of TA words, the outbox entries of two
+// generations (NE each: the tile's islands and the ring around them, or a
+// whole torus), the islands' draws of `draws` generations (the
+// emigration words in 16 bits), then the float births' draw queues.
+struct TileLds {
+    uint32_t TA, NE, obw, entries, imm, act, emig, queue;
+};
+
+__host__ __device__ inline TileLds tile_lds(uint32_t RI, uint32_t NE, uint32_t N, uint32_t SW,
+                                            bool async, uint32_t draws) {
+    TileLds l;
+    l.TA = (RI * N + 3u) & ~3u;
+    l.NE = NE;
+    l.obw = async ? kOutboxWords : kSyncOutboxWords;
+    l.entries = (1u + SW + (async ? 1u : 0u)) * l.TA;
+    l.imm = l.entries + 2u * NE * l.obw;
+    l.act = l.imm + draws * RI;
+    l.emig = l.act + (async ? draws * RI : 0u);
+    l.queue = (l.emig + (draws * RI + 1u) / 2u + 3u) & ~3u;
+    return l;
+}
+
+// The run's key, opaque in tiles: a generation's draws then work out its
+// schedule themselves (kept for all of a launch's draws it would take 20
+// scalar registers; a resident run's loop keeps it).
+template <bool OPAQUE>
+__device__ __forceinline__ uint2 run_key(const StepParams& p) {
+    uint2 k = make_uint2(p.k0, p.k1);
+    if (OPAQUE) asm volatile("" : "+s"(k.x), "+s"(k.y));
+    return k;
+}
+
+// The Philox blocks of K births from slot j on (and the second blocks of
 // float births), computed as interleaved chains.  Their counter words
-// (slot, island, generation, purpose) need no population data, so the tile
-// computes them while its loads are in flight.
-template <uint32_t BM, int APT>
+// (slot, island, generation, purpose) need no population data.
+template <uint32_t BM, int K>
 struct BirthDraws {
-    static constexpr int NB = BM == kBirthFloat ? 2 * APT : APT;
+    static constexpr int NB = BM == kBirthFloat ? 2 * K : K;
     uint4 blk[NB];
-    __device__ __forceinline__ void compute(const StepParams& p, uint32_t j0, uint32_t isl) {
+    __device__ __forceinline__ void compute(uint2 key, uint32_t j, uint32_t isl, uint32_t g) {
 #pragma unroll
-        for (int q = 0; q < APT; ++q) {
-            blk[q] = make_uint4(j0 + q, isl, p.g, kBirth);
-            if constexpr (BM == kBirthFloat) blk[APT + q] = make_uint4(j0 + q, isl, p.g, kBirthB);
+        for (int q = 0; q < K; ++q) {
+            blk[q] = make_uint4(j + q, isl, g, kBirth);
+            if constexpr (BM == kBirthFloat) blk[K + q] = make_uint4(j + q, isl, g, kBirthB);
         }
-        philox4x32_10_multi<NB>(blk, p.k0, p.k1);
+        philox4x32_10_multi<NB>(blk, key.x, key.y);
     }
 };
 
-// Births of this thread's APT agents.  APT divides N, so they share one
-// island (il of the tile, slots j0 .. j0+APT-1).
-template <int SW, uint32_t BM, bool MIGR, int APT, bool ASYNC, bool POW2>
-__device__ __forceinline__ void step_births(const StepParams& p, uint32_t first_isl,
-                                            uint32_t la0, uint32_t il, uint32_t j0,
-                                            const BirthDraws<BM, APT>& draws,
-                                            uint32_t site_word, uint32_t site_shift,
-                                            uint32_t diff_mask, uint32_t n_shift) {
-    uint32_t* lds = g_step_lds;
-    const uint32_t N = p.N;
-    const uint32_t TA = (p.tile_isl * N + 3u) & ~3u;
-    const uint32_t* l_trait = lds;
-    const uint32_t* l_count = lds + TA;
-    const uint32_t* l_surf = lds + 2 * TA;
-    const uint32_t* l_plan = lds + (2 + SW) * TA;
-    const uint32_t* l_emig = l_plan + p.tile_isl;
-    const size_t a0 = (size_t)first_isl * N;
-    const size_t A = p.A;
-    auto pick = [&](uint32_t w) -> uint32_t {
-        if constexpr (POW2) return w >> n_shift;   // = mulhi(w, N) for N = 2^(32 - n_shift)
-        else return word_below(w, N);
-    };
-    const uint32_t isl = first_isl + il;
-    const uint32_t base = il * N;
-    const uint4* blk = draws.blk;
-    Lanes<APT> ctr, ccn, csf[SW];
-    // Float births: the half-normal draws of the mutating births are queued
-    // in the wave's LDS area (cosine cases from the front, sine cases from
-    // the back) and evaluated after the loop in rounds of the wave's lanes,
-    // so the draw runs once per mutating birth rather than once per birth
-    // for the whole wave, and no round mixes the two series.
-    // The loop itself has only wave-uniform branches; the mutation class of
-    // each birth is read again from its draw words after the loop, where the
-    // queue is filled.
-    constexpr uint32_t QC = 64u * APT;                  // queue capacity of a wave
-    uint2* wq = nullptr;
-    uint32_t fslot = 0, ncos = 0, nsin = 0;
-    if constexpr (BM == kBirthFloat)
-        wq = reinterpret_cast<uint2*>(lds + ((((2 + SW) * TA + 2 * p.tile_isl) + 3u) & ~3u)) +
-             (threadIdx.x >> 6) * QC;
+// A slot draw onto [0, N): a shift when N is a power of two above 1
+// (n_shift = 32 - log2 N), which mulhi(w, N) then equals.
+template <bool POW2>
+__device__ __forceinline__ uint32_t pick_slot(uint32_t w, uint32_t N, uint32_t n_shift) {
+    if constexpr (POW2) return w >> n_shift;
+    else return word_below(w, N);
+}
+
+// Where a birth deposits: the bits of the two surface words that its
+// differentia replaces (none between ingests) and their offset.
+struct Deposit {
+    uint32_t mask[2], shift;
+};
+
+__device__ __forceinline__ Deposit deposit_at(uint32_t site, uint32_t diff_log2) {
+    const uint32_t shift = (site << diff_log2) & 31u;
+    const uint32_t m = (diff_log2 ? 0xffu : 1u) << shift;
+    const bool second = (site >> (5u - diff_log2)) != 0u;
+    return {{second ? 0u : m, second ? m : 0u}, shift};
+}
+
+// ... of an asynchronous birth: the parent's own counter T picks the item
+// and, in constant time through the rule's tables, its site.
+__device__ __forceinline__ Deposit deposit_of(const StepParams& p, uint32_t T) {
+    const uint32_t tau = p.interval == 1u ? T : T / p.interval;
+    if (tau * p.interval != T) return {{0u, 0u}, 0u};
+    return deposit_at(tau >= p.ring_lo ? p.ring[tau & (kSiteRing - 1u)]
+                                       : scheme_site(p.rules, p.kind, p.S, tau),
+                      p.diff_log2);
+}
+
+// Surface word w with the differentia's low bits deposited (one v_bfi_b32
+// after the shift).
+__device__ __forceinline__ uint32_t deposited(uint32_t word, int w, const Deposit& d,
+                                              uint32_t bits) {
+    return (word & ~d.mask[w]) | ((bits << d.shift) & d.mask[w]);
+}
+
+// ... of generation g of a synchronous run, whose parents all carry
+// counter g: the batch's schedule.
+__device__ __forceinline__ Deposit scheduled_deposit(const StepParams& p, uint32_t g) {
+    const uint32_t tau = p.interval == 1u ? g : g / p.interval;
+    if (tau * p.interval != g) return {{0u, 0u}, 0u};
+    return deposit_at(p.sites[tau - p.tau0], p.diff_log2);
+}
+
+__device__ __forceinline__ uint32_t int_mutation(const StepParams& p, uint32_t test,
+                                                 uint32_t amount) {
+    return test < p.mut_thr ? (uint32_t)((int32_t)word_below(amount, p.mut_span) + p.mut_lo) : 0u;
+}
+
+// A mutating float birth: deleterious below del_thr, beneficial in the top
+// ben_thr words.
+__device__ __forceinline__ bool float_mutates(const StepParams& p, uint32_t class_word) {
+    return class_word < p.del_thr || (p.ben_thr != 0u && class_word >= 0u - p.ben_thr);
+}
+
+// An outbox entry: direction (4: none), trait, counter (asynchronous
+// ticks), surface words.
+struct Emigrant {
+    uint32_t dir, trait, counter, s0, s1;
+};
+
+template <bool ASYNC>
+__device__ __forceinline__ void post_entry(uint32_t* o, const Emigrant& e) {
+    if constexpr (!ASYNC) {
+        // synchronous: always a direction below 4, counter implied
+        *reinterpret_cast<uint4*>(o) = make_uint4(e.dir, e.trait, e.s0, e.s1);
+    } else if (e.dir < 4u) {
+        *reinterpret_cast<uint4*>(o) = make_uint4(e.dir, e.trait, e.counter, e.s0);
+        *reinterpret_cast<uint4*>(o + 4) = make_uint4(e.s1, 0u, 0u, 0u);
+    } else {
+        *reinterpret_cast<uint4*>(o) = make_uint4(e.dir, 0u, 0u, 0u);
+        *reinterpret_cast<uint4*>(o + 4) = make_uint4(0u, 0u, 0u, 0u);
+    }
+}
+
+// The emigrant that an island around a tile posts in generation p.g, its
+// slot and direction drawn already: that slot's birth, from P_g and O_g in
+// memory.  A drawn candidate is an immigrant where the last arrival written
+// to its slot says so.  load() issues everything the birth may need at once
+// (a float birth's surface, of up to five candidates, is left until its
+// parent is known), so that the few lanes that work one out wait once, and
+// that behind the loads of the tile and the birth draws; child() is the
+// birth.
+template <int SW, uint32_t BM, bool ASYNC>
+struct RingBirth {
+    static constexpr uint32_t OBW = ASYNC ? kOutboxWords : kSyncOutboxWords;
+    static constexpr bool FLOAT = BM == kBirthFloat;
+    static constexpr int NC = FLOAT ? 5 : (BM == kBirthIntTournament ? 2 : 1);
+    uint4 en[4];                          // the neighbours' entries (SW > 1 ticks: and hi)
+    uint32_t hi[4];
+    uint32_t tr[NC], cn[NC], sf[NC][SW];  // the candidates' records
+    uint32_t slots;                       // 6 bits per candidate
+    uint32_t match;                       // bit 4c + d: direction d's immigrant has c's slot
+    uint32_t w0, w1, w2;                  // int: r.z, r.w; float: v.y, v.z, v.w
+    size_t a0;                            // the island's first agent
+
+    __device__ __forceinline__ void load(const StepParams& p, uint32_t isl, uint32_t x,
+                                         uint32_t slot) {
+        const uint32_t N = p.N;
 #pragma unroll
-    for (int q = 0; q < APT; ++q) {
-        const uint32_t la = la0 + q;
-        bool act = true;
-        if constexpr (ASYNC) act = (l_plan[il] >> 31) != 0u;
-        if (!act) {
-            // idle island: the same individual on the next tick
-            ctr.v[q] = l_trait[la];
-            ccn.v[q] = l_count[la];
+        for (uint32_t d = 0; d < 4; ++d) {
+            const uint32_t* o = p.ob_in + (size_t)neighbour_of(isl, x, d, p.W, p.I) * OBW;
+            en[d] = *reinterpret_cast<const uint4*>(o);
+            if (ASYNC && SW > 1) hi[d] = o[4];
+        }
+        uint4 b[FLOAT ? 3 : 2];
+        b[0] = make_uint4(slot, isl, p.g, kBirth);
+        b[1] = make_uint4(0u, isl, p.g, kImmigrate);
+        if constexpr (FLOAT) b[2] = make_uint4(slot, isl, p.g, kBirthB);
+        const uint2 key = run_key<true>(p);
+        philox4x32_10_multi<FLOAT ? 3 : 2>(b, key.x, key.y);
+        const uint4 r = b[0];
+        const uint4 v = b[FLOAT ? 2 : 0];
+        const uint32_t words[5] = {r.x, r.y, r.z, r.w, v.x};
+        const uint32_t imm[4] = {word_below(b[1].x, N), word_below(b[1].y, N),
+                                 word_below(b[1].z, N), word_below(b[1].w, N)};
+        a0 = (size_t)isl * N;
+        slots = 0;
+        match = 0;
 #pragma unroll
-            for (int w = 0; w < SW; ++w) csf[w].v[q] = l_surf[w * TA + la];
-        } else {
-            const uint4 r = blk[q];
-            uint32_t par = base + pick(r.x);
-            uint32_t bit;
-            if constexpr (BM == kBirthFloat) {
-                // tournament of p.tour draws (words r.x, r.y, r.z, r.w, v.x),
-                // the first of maximal fitness winning; mutation class from
-                // v.y, |Z| from v.z and v.w, differentia the low bits of v.w
-                const uint4 v = blk[APT + q];
-                float best = __uint_as_float(l_trait[par]);
-                const uint32_t words[4] = {r.y, r.z, r.w, v.x};
+        for (int c = 0; c < NC; ++c) {
+            const uint32_t cand = word_below(words[c], N);
+            tr[c] = p.in_trait[a0 + cand];
+            if constexpr (!FLOAT) {
+                if constexpr (ASYNC) cn[c] = p.in_counter[a0 + cand];
 #pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    if ((uint32_t)c + 1u < p.tour) {
-                        const uint32_t cb = base + pick(words[c]);
-                        const float fc = __uint_as_float(l_trait[cb]);
-                        if (fc > best) {
-                            best = fc;
-                            par = cb;
-                        }
-                    }
-                }
-                ctr.v[q] = __float_as_uint(best);        // the draw is applied after the loop
-                bit = v.w & diff_mask;
+                for (int w = 0; w < SW; ++w) sf[c][w] = p.in_surf[(size_t)w * p.A + a0 + cand];
+            }
+            slots |= cand << (6 * c);
+#pragma unroll
+            for (uint32_t d = 0; d < 4; ++d) match |= (imm[d] == cand ? 1u : 0u) << (4 * c + d);
+        }
+        // before the first generation no entry was posted
+        if (!p.has_inbox) match = 0;
+        w0 = FLOAT ? v.y : r.z;
+        w1 = FLOAT ? v.z : r.w;
+        w2 = FLOAT ? v.w : r.w;
+    }
+
+    __device__ __forceinline__ Emigrant child(const StepParams& p, uint32_t dir, Deposit dep) {
+        // a neighbour delivers when its emigrant was sent our way
+        uint32_t sent = 0;
+#pragma unroll
+        for (uint32_t d = 0; d < 4; ++d) sent |= (en[d].x == (d ^ 1u) ? 1u : 0u) << d;
+        uint32_t best = 0, src = 0, par = 0, T = p.g, s[SW] = {};
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            // the directions whose immigrant candidate c is; the last one wins
+            const uint32_t arr = (match >> (4 * c)) & sent;
+            uint32_t t = tr[c];
+#pragma unroll
+            for (uint32_t d = 0; d < 4; ++d) {
+                const uint32_t y = en[d].y;
+                t = (arr >> d) & 1u ? y : t;
+            }
+            bool win = c == 0;
+            if constexpr (FLOAT)
+                win = win || ((uint32_t)c < p.tour && __uint_as_float(t) > __uint_as_float(best));
+            else
+                win = win || (int32_t)t > (int32_t)best;
+            best = win ? t : best;
+            src = win ? arr : src;
+            if constexpr (FLOAT) {
+                par = win ? (slots >> (6 * c)) & 63u : par;
             } else {
-                uint32_t ptrait = l_trait[par];
-                if constexpr (BM == kBirthIntTournament) {
-                    const uint32_t pb = base + pick(r.y);
-                    const uint32_t tb = l_trait[pb];
-                    if ((int32_t)tb > (int32_t)ptrait) {
-                        par = pb;
-                        ptrait = tb;
-                    }
+                if constexpr (ASYNC) {
+                    const uint32_t n = cn[c];
+                    T = win ? n : T;
                 }
-                const uint32_t delta =
-                    r.z < p.mut_thr ? (uint32_t)((int32_t)word_below(r.w, p.mut_span) + p.mut_lo)
-                                    : 0u;
-                ctr.v[q] = ptrait + delta;
-                bit = r.w & diff_mask;
-            }
-            // synchronous generations: every member's counter is g
-            const uint32_t T = ASYNC ? l_count[par] : p.g;
-            ccn.v[q] = T + 1u;
-            uint32_t dep_word = site_word, dep_shift = site_shift;
-            if constexpr (ASYNC) {
-                // the parent's own counter picks the item and, in constant
-                // time through the rule's tables, its site
-                const uint32_t tau = p.interval == 1u ? T : T / p.interval;
-                dep_word = 0xffu;
-                if (tau * p.interval == T) {
-                    const uint32_t site = tau >= p.ring_lo
-                                              ? p.ring[tau & (kSiteRing - 1u)]
-                                              : scheme_site(p.rules, p.kind, p.S, tau);
-                    dep_word = site >> (5u - p.diff_log2);
-                    dep_shift = (site << p.diff_log2) & 31u;
-                }
-            }
 #pragma unroll
-            for (int w = 0; w < SW; ++w) {
-                const uint32_t word = l_surf[w * TA + par];
-                csf[w].v[q] = (uint32_t)w == dep_word
-                                  ? (word & ~(diff_mask << dep_shift)) | (bit << dep_shift)
-                                  : word;
+                for (int w = 0; w < SW; ++w) {
+                    const uint32_t f = sf[c][w], o = s[w];
+                    s[w] = win ? f : o;
+                }
             }
         }
-    }
-    if constexpr (BM == kBirthFloat) {
-        // mutating births: deleterious below del_thr, beneficial in the top
-        // ben_thr words (idle islands of a tick draw nothing)
-        bool act = true;
-        if constexpr (ASYNC) act = (l_plan[il] >> 31) != 0u;
-        const bool ben_on = p.ben_thr != 0u;
-        const uint32_t ben_lo = 0u - p.ben_thr;
-        auto needs = [&](const uint4& v) {
-            return act && (v.y < p.del_thr || (ben_on && v.y >= ben_lo));
-        };
+        if constexpr (FLOAT) {
+            if constexpr (ASYNC) T = p.in_counter[a0 + par];
 #pragma unroll
-        for (int q = 0; q < APT; ++q) {
-            const uint4 vq = blk[APT + q];
-            const bool nd = needs(vq);
-            const bool sn = vq.w >= 0x80000000u;          // the draw's sine case
-            const uint64_t mc = __ballot(nd && !sn);
-            const uint64_t ms = __ballot(nd && sn);
-            if (nd) {
-                const uint32_t slot = sn ? QC - 1u - (nsin + lanes_below(ms))
-                                         : ncos + lanes_below(mc);
-                wq[slot] = make_uint2(vq.z, vq.w);
+            for (int w = 0; w < SW; ++w) s[w] = p.in_surf[(size_t)w * p.A + a0 + par];
+        }
+#pragma unroll
+        for (uint32_t d = 0; d < 4; ++d) {
+            const bool it = (src >> d) & 1u;
+            const uint4 e = en[d];
+            const uint32_t h = hi[d], f0 = s[0], f1 = s[SW - 1];
+            if constexpr (ASYNC) T = it ? e.z : T;
+            const uint32_t e0 = ASYNC ? e.w : e.z, e1 = ASYNC ? h : e.w;
+            s[0] = it ? e0 : f0;
+            if (SW > 1) s[SW - 1] = it ? e1 : f1;
+        }
+        if constexpr (FLOAT) {
+            if (float_mutates(p, w0)) {
+                const double z = half_normal(w1, w2);
+                best = __float_as_uint(apply_half_normal(
+                    __uint_as_float(best), w0 < p.del_thr ? p.del_scale : p.ben_scale, z));
+            }
+        } else {
+            best += int_mutation(p, w0, w1);
+        }
+        if constexpr (ASYNC) dep = deposit_of(p, T);
+        return {dir, best, T + 1u, deposited(s[0], 0, dep, w2),
+                SW > 1 ? deposited(s[SW - 1], 1, dep, w2) : 0u};
+    }
+};
+
+// The children of a thread's APT births.
+template <int SW, int APT>
+struct Children {
+    Lanes<APT> tr, cn, sf[SW];
+};
+
+// An idle island of an asynchronous tick: the same individuals on the next.
+template <int SW, int APT>
+__device__ __forceinline__ void keep_agents(const uint32_t* lds, uint32_t TA, uint32_t la0,
+                                            Children<SW, APT>& kid) {
+#pragma unroll
+    for (int q = 0; q < APT; ++q) {
+        kid.tr.v[q] = lds[la0 + q];
+#pragma unroll
+        for (int w = 0; w < SW; ++w) kid.sf[w].v[q] = lds[(1 + w) * TA + la0 + q];
+        kid.cn.v[q] = lds[(1 + SW) * TA + la0 + q];
+    }
+}
+
+// The rest of a birth once its parent (LDS agent par) is chosen: its
+// surface with the differentia (the low bits of `bits`) deposited and, in
+// asynchronous ticks, its counter.  Synchronous generations: every member's
+// counter is the generation and dep its deposit.
+template <int SW, int APT, bool ASYNC>
+__device__ __forceinline__ void inherit(const StepParams& p, const uint32_t* lds, uint32_t TA,
+                                        uint32_t par, uint32_t bits, Deposit dep, int q,
+                                        Children<SW, APT>& kid) {
+    if constexpr (ASYNC) {
+        const uint32_t T = lds[(1 + SW) * TA + par];
+        kid.cn.v[q] = T + 1u;
+        dep = deposit_of(p, T);
+    }
+#pragma unroll
+    for (int w = 0; w < SW; ++w)
+        kid.sf[w].v[q] = deposited(lds[(1 + w) * TA + par], w, dep, bits);
+}
+
+// Integer births of this thread's APT agents.  APT divides N, so they share
+// one island, whose agents start at LDS agent base.
+template <int SW, uint32_t BM, int APT, bool ASYNC, bool POW2>
+__device__ __forceinline__ void step_births(const StepParams& p, const uint32_t* lds, uint32_t TA,
+                                            uint32_t base, const BirthDraws<BM, APT>& draws,
+                                            const Deposit& dep, uint32_t n_shift,
+                                            Children<SW, APT>& kid) {
+    const uint32_t* l_trait = lds;
+#pragma unroll
+    for (int q = 0; q < APT; ++q) {
+        const uint4 r = draws.blk[q];
+        uint32_t par = base + pick_slot<POW2>(r.x, p.N, n_shift);
+        uint32_t ptrait = l_trait[par];
+        if constexpr (BM == kBirthIntTournament) {
+            const uint32_t pb = base + pick_slot<POW2>(r.y, p.N, n_shift);
+            const uint32_t tb = l_trait[pb];
+            if ((int32_t)tb > (int32_t)ptrait) {
+                par = pb;
+                ptrait = tb;
+            }
+        }
+        kid.tr.v[q] = ptrait + int_mutation(p, r.z, r.w);
+        inherit<SW, APT, ASYNC>(p, lds, TA, par, r.w, dep, q, kid);
+    }
+}
+
+// Float births of this thread's APT agents (slots j0 on of island isl),
+// drawn and chosen two at a time: four chains are enough to overlap, and
+// the blocks of all four births at once would take the registers of two
+// wavefronts per SIMD.  The half-normal draws of the mutating births are
+// queued in the wave's LDS area wq (64 APT entries: cosine cases from the
+// front, sine cases from the back) and evaluated after all births in rounds
+// of the wave's lanes, so the draw runs once per mutating birth rather than
+// once per birth for the whole wave, and no round mixes the two series.
+template <int SW, int APT, bool ASYNC, bool POW2>
+__device__ __forceinline__ void step_float_births(const StepParams& p, const uint32_t* lds,
+                                                  uint32_t TA, uint32_t base, uint32_t j0,
+                                                  uint32_t isl, uint32_t g, const Deposit& dep,
+                                                  uint32_t n_shift, uint2* wq,
+                                                  Children<SW, APT>& kid) {
+    constexpr int K = APT < 2 ? APT : 2;
+    constexpr uint32_t QC = 64u * APT;
+    const uint32_t* l_trait = lds;
+    uint32_t fslot = 0, ncos = 0, nsin = 0;
+    bool mutates[APT], worse[APT];
+    const uint2 key = run_key<true>(p);
+#pragma unroll
+    for (int q0 = 0; q0 < APT; q0 += K) {
+        BirthDraws<kBirthFloat, K> draws;
+        draws.compute(key, j0 + q0, isl, g);
+#pragma unroll
+        for (int i = 0; i < K; ++i) {
+            // tournament of p.tour draws (words r.x, r.y, r.z, r.w, v.x),
+            // the first of maximal fitness winning; mutation class from
+            // v.y, |Z| from v.z and v.w, differentia the low bits of v.w
+            const int q = q0 + i;
+            const uint4 r = draws.blk[i], v = draws.blk[K + i];
+            uint32_t par = base + pick_slot<POW2>(r.x, p.N, n_shift);
+            float best = __uint_as_float(l_trait[par]);
+            const uint32_t words[4] = {r.y, r.z, r.w, v.x};
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                if ((uint32_t)c + 1u < p.tour) {
+                    const uint32_t cb = base + pick_slot<POW2>(words[c], p.N, n_shift);
+                    const float fc = __uint_as_float(l_trait[cb]);
+                    if (fc > best) {
+                        best = fc;
+                        par = cb;
+                    }
+                }
+            }
+            kid.tr.v[q] = __float_as_uint(best);         // the draw is applied below
+            inherit<SW, APT, ASYNC>(p, lds, TA, par, v.w, dep, q, kid);
+            mutates[q] = float_mutates(p, v.y);
+            worse[q] = v.y < p.del_thr;
+            const bool sn = v.w >= 0x80000000u;          // the draw's sine case
+            const uint64_t mc = __ballot(mutates[q] && !sn);
+            const uint64_t ms = __ballot(mutates[q] && sn);
+            if (mutates[q]) {
+                const uint32_t slot = sn ? QC - 1u - lanes_below(ms, nsin) : lanes_below(mc, ncos);
+                wq[slot] = make_uint2(v.z, v.w);
                 fslot |= slot << (8 * q);
             }
             ncos += (uint32_t)__popcll(mc);
             nsin += (uint32_t)__popcll(ms);
         }
-        // the queued draws in rounds of the active lanes (one wavefront: its
-        // LDS writes land before its later reads), then each birth's fitness
-        const uint64_t ex = __ballot(true);
-        const uint32_t me = lanes_below(ex), na = (uint32_t)__popcll(ex);
-        for (uint32_t b0 = 0; b0 < ncos; b0 += na) {
-            if (b0 + me < ncos) {
-                const uint2 e = wq[b0 + me];
-                const double z = half_normal_case<false>(e.x, e.y);
-                const uint64_t zb = (uint64_t)__double_as_longlong(z);
-                wq[b0 + me] = make_uint2((uint32_t)zb, (uint32_t)(zb >> 32));
-            }
-        }
-        for (uint32_t b0 = 0; b0 < nsin; b0 += na) {
-            if (b0 + me < nsin) {
-                const uint32_t i = QC - 1u - (b0 + me);
+    }
+    // the queued draws in rounds of the active lanes (one wavefront: its
+    // LDS writes land before its later reads), then each birth's fitness
+    const uint64_t ex = __ballot(true);
+    const uint32_t me = lanes_below(ex), na = (uint32_t)__popcll(ex);
+    auto evaluate = [&](uint32_t n, bool sine) __attribute__((always_inline)) {
+        for (uint32_t b0 = 0; b0 < n; b0 += na) {
+            if (b0 + me < n) {
+                const uint32_t i = sine ? QC - 1u - (b0 + me) : b0 + me;
                 const uint2 e = wq[i];
-                const double z = half_normal_case<true>(e.x, e.y);
+                const HalfNormalCoefficients K = half_normal_coefficients();
+                double z = half_normal_radius(K, e.x);
+                if (sine) z *= half_normal_angle<true>(K, e.y);
+                else z *= half_normal_angle<false>(K, e.y);
                 const uint64_t zb = (uint64_t)__double_as_longlong(z);
                 wq[i] = make_uint2((uint32_t)zb, (uint32_t)(zb >> 32));
             }
         }
+    };
+    evaluate(ncos, false);
+    evaluate(nsin, true);
 #pragma unroll
-        for (int q = 0; q < APT; ++q) {
-            const uint4 vq = blk[APT + q];
-            if (needs(vq)) {
-                const uint2 e = wq[(fslot >> (8 * q)) & 0xffu];
-                const double z =
-                    __longlong_as_double((long long)(((uint64_t)e.y << 32) | e.x));
-                ctr.v[q] = __float_as_uint(apply_half_normal(__uint_as_float(ctr.v[q]),
-                                                             vq.y < p.del_thr, p.del_sigma,
-                                                             p.ben_sigma, z));
-            }
+    for (int q = 0; q < APT; ++q) {
+        if (mutates[q]) {
+            const uint2 e = wq[(fslot >> (8 * q)) & 0xffu];
+            const double z = __longlong_as_double((long long)(((uint64_t)e.y << 32) | e.x));
+            kid.tr.v[q] = __float_as_uint(apply_half_normal(
+                __uint_as_float(kid.tr.v[q]), worse[q] ? p.del_scale : p.ben_scale, z));
         }
     }
-    if (MIGR) {
-        // the island's emigrant, if it is one of this thread's agents (after
-        // the loop, so that the loop body has no branch and the agents' LDS
-        // reads overlap)
-        const uint32_t em = l_emig[il];
-        const uint32_t qe = (em & 0xffu) - j0;          // >= APT: another thread's
-        constexpr uint32_t OBW = ASYNC ? kOutboxWords : kSyncOutboxWords;
-        if (qe < (uint32_t)APT) {
-            uint32_t e_tr = ctr.v[0], e_cn = ccn.v[0], e_s0 = csf[0].v[0],
-                     e_s1 = csf[SW - 1].v[0];
-#pragma unroll
-            for (int q = 1; q < APT; ++q) {
-                if (qe == (uint32_t)q) {
-                    e_tr = ctr.v[q];
-                    e_cn = ccn.v[q];
-                    e_s0 = csf[0].v[q];
-                    e_s1 = csf[SW - 1].v[q];
-                }
-            }
-            uint32_t* o = p.ob_out + (size_t)isl * OBW;
-            const uint32_t dir = (em >> 8) & 7u;
-            if constexpr (!ASYNC) {
-                // synchronous: always a direction below 4, counter implied
-                *reinterpret_cast<uint4*>(o) = make_uint4(dir, e_tr, e_s0, SW > 1 ? e_s1 : 0u);
-            } else if (dir < 4u) {
-                *reinterpret_cast<uint4*>(o) = make_uint4(dir, e_tr, e_cn, e_s0);
-                *reinterpret_cast<uint4*>(o + 4) = make_uint4(SW > 1 ? e_s1 : 0u, 0u, 0u, 0u);
-            } else {
-                *reinterpret_cast<uint4*>(o) = make_uint4(dir, 0u, 0u, 0u);
-                *reinterpret_cast<uint4*>(o + 4) = make_uint4(0u, 0u, 0u, 0u);
-            }
-        }
-    }
-    store_lanes<APT>(p.out_trait + a0 + la0, ctr);
-    // a synchronous run keeps no counter plane: every counter is g + 1
-    if constexpr (ASYNC) store_lanes<APT>(p.out_counter + a0 + la0, ccn);
-#pragma unroll
-    for (int w = 0; w < SW; ++w) store_lanes<APT>(p.out_surf + w * A + a0 + la0, csf[w]);
 }
 
-
-// One tile of one run.  Shared by the plain kernel (one run per launch) and
-// the batched kernel (many runs per launch).
-template <int SW, uint32_t BM, bool MIGR, int APT, bool ASYNC = false>
+// One tile of one run.  Shared by the plain kernel (one run per launch),
+// the batched kernel (many runs per launch) and the resident kernel (WHOLE:
+// the tile is the whole torus, so its islands' neighbours are its own and
+// any number of generations follow one another in LDS).
+template <int SW, uint32_t BM, bool MIGR, int APT, bool ASYNC, bool WHOLE>
 __device__ __forceinline__ void step_tile(const StepParams& p, uint32_t tile) {
+    constexpr uint32_t OBW = ASYNC ? kOutboxWords : kSyncOutboxWords;
     uint32_t* lds = g_step_lds;
-    const uint32_t N = p.N, W = p.W;
-    const uint32_t TA = (p.tile_isl * N + 3u) & ~3u;   // plane stride (16-byte multiple)
+    const uint32_t N = p.N, W = p.W, H = p.H;
+    const uint32_t TW = p.tile.w, RI = p.tile.w * p.tile.h;   // WHOLE: W and I
+    const uint32_t PW = WHOLE ? W : TW + 2u;                  // entries per row
+    const TileLds L = tile_lds(RI, WHOLE ? RI : PW * (p.tile.h + 2u), N, SW, ASYNC,
+                              WHOLE ? p.tile.draws : kTileGens);
+    const uint32_t TA = L.TA;
     uint32_t* l_trait = lds;
-    uint32_t* l_count = lds + TA;
-    uint32_t* l_surf = lds + 2 * TA;                   // SW planes of TA words
-    uint32_t* l_plan = lds + (2 + SW) * TA;            // tile_isl words
-    uint32_t* l_emig = l_plan + p.tile_isl;            // tile_isl words
-
-    const uint32_t first_isl = tile * p.tile_isl;
-    const uint32_t nisl = min(p.tile_isl, p.I - first_isl);
-    const uint32_t nag = nisl * N;
-    const size_t a0 = (size_t)first_isl * N;
+    uint32_t* l_surf = lds + TA;                       // SW planes of TA words
+    uint32_t* l_count = lds + (1 + SW) * TA;           // asynchronous ticks only
+    uint32_t* l_imm = lds + L.imm;                     // [draws][RI]
+    uint32_t* l_act = lds + L.act;                     // the same, asynchronous ticks only
+    uint16_t* l_emig = reinterpret_cast<uint16_t*>(lds + L.emig);   // the same
     const size_t A = p.A;
     const uint32_t t = threadIdx.x;
     const uint32_t la0 = t * APT;
-    const bool mine = la0 < nag;
 
-    // this generation's deposit: word and bit offset of the site, none
-    // (no word matches) between ingests
-    uint32_t site_word = 0xffu, site_shift = 0u;
-    if (p.site) {
-        const uint32_t site = *p.site;
-        site_word = site >> (5u - p.diff_log2);
-        site_shift = (site << p.diff_log2) & 31u;
+    // the tile's islands: columns x0 .. x0 + vw - 1, rows y0 .. y0 + vh - 1
+    uint32_t x0 = 0, y0 = 0, vw = W, vh = H;
+    if constexpr (!WHOLE) {
+        const uint32_t ty = quotient_of(tile, p.tile.cols_magic, p.tile.cols_shift);
+        x0 = (tile - ty * p.tile.cols) * TW;
+        y0 = ty * p.tile.h;
+        vw = min(TW, W - x0);
+        vh = min(p.tile.h, H - y0);
     }
+    // this thread's island (il of the tile, isl of the run, its entry at
+    // eidx) and first slot (one division: la0 < 4096)
+    const uint32_t il = (la0 * p.tile.n_magic) >> 20;
+    const uint32_t j0 = la0 - il * N;
+    bool mine = il < RI;
+    uint32_t isl = il, eidx = il;
+    if constexpr (!WHOLE) {
+        const uint32_t ly = (il * p.tile.w_magic) >> 20, lx = il - ly * TW;
+        mine = mine && lx < vw && ly < vh;
+        isl = (y0 + ly) * W + x0 + lx;
+        eidx = (ly + 1u) * PW + lx + 1u;
+    }
+    const uint32_t ga = isl * N + j0;
+
     // A wave issues its loads at the highest priority and then drops back:
     // when a fresh wave arrives, its loads go out ahead of the arithmetic of
     // waves already holding data, which keeps more bytes in flight.
@@ -505,296 +719,437 @@ __device__ __forceinline__ void step_tile(const StepParams& p, uint32_t tile) {
     // 1. this thread's agents, every plane
     Lanes<APT> tr, ct, sf[SW];
     if (mine) {
-        tr = load_lanes<APT>(p.in_trait + a0 + la0);
+        tr = load_lanes<APT>(p.in_trait, ga);
         // only asynchronous runs keep a counter plane: in synchronous
         // generations every agent's counter is the generation number
         // (founders 0, each birth one above a parent of the same
         // generation)
-        if (ASYNC) ct = load_lanes<APT>(p.in_counter + a0 + la0);
+        if (ASYNC) ct = load_lanes<APT>(p.in_counter, ga);
 #pragma unroll
-        for (int w = 0; w < SW; ++w) sf[w] = load_lanes<APT>(p.in_surf + w * A + a0 + la0);
+        for (int w = 0; w < SW; ++w) sf[w] = load_lanes<APT>(p.in_surf + w * A, ga);
     }
-    // Island pass: thread t takes island t for immigration (and the activity
-    // draw) and thread blockDim-1-t takes island t for emigration; the host
-    // keeps tile_isl <= blockDim.  Each neighbour's whole outbox entry is
-    // read together with the tile (the record shares the direction word's
-    // cache line), so the immigrants need no second round trip; the loads
-    // are issued outside any branch (lanes without an island read entry 0;
-    // before the first generation the entries are read but not used) so
-    // that nothing waits for them before the birth draws.  Only wavefronts
-    // holding an island lane work out neighbour indices (a wave-uniform
-    // test: most wavefronts of a large tile hold none); the loads stay after
-    // the branch, since loads inside it would be waited for at its end.
-    constexpr uint32_t OBW = ASYNC ? kOutboxWords : kSyncOutboxWords;
-    uint4 in_lo[4], in_hi[4];
-    uint32_t imm_slots = 0;        // the four directions' slots, 6 bits each
-    bool imm_take = false;         // this lane's island takes immigrants
-    if (MIGR) {
-        size_t e[4] = {0, 0, 0, 0};
-        if ((uint32_t)__builtin_amdgcn_readfirstlane((int)t) < nisl) {
-            const bool lane_isl = t < nisl;
-            const uint32_t isl = first_isl + (lane_isl ? t : 0u);
-            const uint32_t x = column_of(isl, W, p.w_magic, p.w_shift);
-#pragma unroll
-            for (int d = 0; d < 4; ++d)
-                e[d] = lane_isl ? (size_t)neighbour_of(isl, x, (uint32_t)d, W, p.I) * OBW : 0;
-        }
-#pragma unroll
-        for (int d = 0; d < 4; ++d) {
-            in_lo[d] = *reinterpret_cast<const uint4*>(p.ob_in + e[d]);
-            if (ASYNC && SW > 1) in_hi[d] = *reinterpret_cast<const uint4*>(p.ob_in + e[d] + 4);
+    // Entry e of the tile's entries: the outbox of its island (the ring's
+    // corners and what a ragged tile leaves out read entry 0, unused).  The
+    // first round's loads are issued outside any branch (before the first
+    // generation the entries are read but not used) so that nothing waits
+    // for them before the birth draws.
+    auto outbox_at = [&](uint32_t e) -> size_t {
+        if constexpr (WHOLE) return e < RI ? (size_t)e * OBW : 0;
+        const uint32_t py = quotient_of(e, p.tile.pw_magic, p.tile.pw_shift), px = e - py * PW;
+        if (px > vw + 1u || py > vh + 1u) return 0;
+        // the ring wraps round the torus (vw <= W: at most twice)
+        uint32_t x = x0 + W - 1u + px, y = y0 + H - 1u + py;
+        x -= x >= W ? W : 0u;
+        x -= x >= W ? W : 0u;
+        y -= y >= H ? H : 0u;
+        y -= y >= H ? H : 0u;
+        return ((size_t)y * W + x) * OBW;
+    };
+    uint4 in_lo, in_hi;
+    if constexpr (MIGR) {
+        // (a wave-uniform test: most wavefronts of a large tile load none)
+        if ((uint32_t)__builtin_amdgcn_readfirstlane((int)t) < L.NE) {
+            const uint32_t* o = p.ob_in + (t < L.NE ? outbox_at(t) : 0);
+            in_lo = *reinterpret_cast<const uint4*>(o);
+            if (ASYNC && SW > 1) in_hi = *reinterpret_cast<const uint4*>(o + 4);
         }
     }
     __builtin_amdgcn_s_setprio(0);
-    if (MIGR && !ASYNC && 2u * nisl <= blockDim.x) {
-        // one Philox evaluation for both island draws: lanes t < nisl draw
-        // island t's immigration block, lanes nisl .. 2 nisl - 1 the
-        // emigration block of island t - nisl (the same blocks as two
-        // separate passes, without a second divergent evaluation)
-        const bool imm_lane = t < nisl;
-        if (t < 2u * nisl) {
-            const uint32_t il = imm_lane ? t : t - nisl;
-            const uint32_t isl = first_isl + il;
-            const uint4 w4 = philox4x32_10(
-                make_uint4(0u, isl, p.g, imm_lane ? kImmigrate : kEmigrate), p.k0, p.k1);
-            if (!imm_lane) {
-                l_emig[il] = word_below(w4.x, N) | ((w4.y >> 30) << 8);
-            } else if (p.has_inbox) {
-                imm_slots = word_below(w4.x, N) | (word_below(w4.y, N) << 6) |
-                            (word_below(w4.z, N) << 12) | (word_below(w4.w, N) << 18);
-                imm_take = true;
-            }
-        }
-    } else if (MIGR || ASYNC) {
-        // asynchronous ticks: an island runs a generation iff its activity
-        // draw is below the threshold (plan bit 31); an idle island takes no
-        // immigrants and posts no emigrant (direction 4)
-        if (t < nisl) {
-            const uint32_t isl = first_isl + t;
-            bool act = true;
-            if constexpr (ASYNC)
-                act = philox4x32_10(make_uint4(0u, isl, p.g, kActivity), p.k0, p.k1).x <
-                      p.async_thr;
-            if (MIGR && act && p.has_inbox) {
-                const uint4 w4 = philox4x32_10(make_uint4(0u, isl, p.g, kImmigrate), p.k0, p.k1);
-                imm_slots = word_below(w4.x, N) | (word_below(w4.y, N) << 6) |
-                            (word_below(w4.z, N) << 12) | (word_below(w4.w, N) << 18);
-                imm_take = true;
-            }
-            if constexpr (ASYNC) l_plan[t] = act ? 1u << 31 : 0u;
-        }
-        if (MIGR) {
-            const uint32_t il = blockDim.x - 1u - t;
-            if (il < nisl) {
-                const uint32_t isl = first_isl + il;
-                bool act = true;
-                if constexpr (ASYNC)
-                    act = philox4x32_10(make_uint4(0u, isl, p.g, kActivity), p.k0, p.k1).x <
-                          p.async_thr;
-                const uint4 w4 = philox4x32_10(make_uint4(0u, isl, p.g, kEmigrate), p.k0, p.k1);
-                l_emig[il] = word_below(w4.x, N) | ((act ? (w4.y >> 30) : 4u) << 8);
-            }
-        }
-    }
 
-    // this thread's island and first slot (one division: la0 < 4096), and
-    // its birth draws while the loads are in flight (integer births; the
-    // float births' two blocks per agent would cost a wave per SIMD, so
-    // they are drawn after the staging)
-    const uint32_t il = (la0 * p.div_magic) >> 20;
-    const uint32_t j0 = la0 - il * N;
+    const uint32_t n_shift = (N > 1u && (N & (N - 1u)) == 0u) ? 32u - __builtin_ctz(N) : 0u;
+    // islands per wavefront, where every island's agents belong to one: its
+    // LDS accesses are in order, so only the entries need a workgroup barrier
+    // (a resident run, whose generations are a chain of latencies; 0: the
+    // tile's last wavefronts take all its islands' immigrants, which is the
+    // least work)
+    const uint32_t own = WHOLE && 64u * APT % N == 0u ? 64u * APT / N : 0u;
+    const bool ring = MIGR && !WHOLE && p.gens > 1u;   // the emigrants of the islands around
     BirthDraws<BM, APT> draws;
-    if constexpr (BM != kBirthFloat)
-        if (mine) draws.compute(p, j0, first_isl + il);
-
-    // 2. stage the tile in LDS, then overwrite immigrant slots (north,
-    // south, west, east: a later direction overwrites an earlier one)
+    // The islands' draws, one lane each: immigration, emigration and
+    // (asynchronous ticks) activity, of two generations at once for a
+    // tile's launch of two -- and, with them, the emigration draws of
+    // the islands around: 44 lanes of one evaluation for a tile of 4 x 2
+    // islands.  A resident run draws as many generations' at once as its
+    // threads hold, after the births that read the last of those before.
+    constexpr uint32_t KINDS = (MIGR ? 2u : 0u) + (ASYNC ? 1u : 0u);
+    uint32_t r_isl = 0, r_x = 0, r_pos = 0, r_draw = kEmpty;   // an island around
+    auto draw_islands = [&](uint32_t k) {
+        const uint32_t g = p.g + k;
+        const uint32_t inner = KINDS * (WHOLE ? p.tile.draws : p.gens) * RI;
+        const uint32_t all = inner + (ring ? 2u * (vw + vh) : 0u);
+        for (uint32_t j = t; j < all; j += blockDim.x) {
+            uint32_t at = 0, gen = g, purpose, di, need = 4u;
+            bool around = false;
+            if (!ring || j < inner) {
+                const uint32_t q = WHOLE ? quotient_of(j, p.tile.cols_magic, p.tile.cols_shift)
+                                         : (j * p.tile.isl_magic) >> 20;
+                const uint32_t li = j - q * RI;
+                const uint32_t half = q / (KINDS ? KINDS : 1u);
+                uint32_t kind = q - half * KINDS;
+                gen += half;
+                at = half * RI + li;
+                di = li;
+                if constexpr (!WHOLE) {
+                    const uint32_t ly = (li * p.tile.w_magic) >> 20;
+                    di = (y0 + ly) * W + x0 + li - ly * TW;
+                }
+                if (!MIGR) kind = 2u;
+                purpose = kind == 0u ? kImmigrate : (kind == 1u ? kEmigrate : kActivity);
+            } else {
+                // north, south, west, east sides; an emigrant comes in
+                // when it was sent the opposite way
+                around = true;
+                uint32_t h = j - inner, px, py;
+                if (h < 2u * vw) {
+                    const bool s = h >= vw;
+                    px = 1u + h - (s ? vw : 0u);
+                    py = s ? vh + 1u : 0u;
+                    need = s ? 0u : 1u;
+                } else {
+                    h -= 2u * vw;
+                    const bool e = h >= vh;
+                    py = 1u + h - (e ? vh : 0u);
+                    px = e ? vw + 1u : 0u;
+                    need = e ? 2u : 3u;
+                }
+                uint32_t x = x0 + W - 1u + px, y = y0 + H - 1u + py;
+                x -= x >= W ? W : 0u;
+                x -= x >= W ? W : 0u;
+                y -= y >= H ? H : 0u;
+                y -= y >= H ? H : 0u;
+                di = y * W + x;
+                r_isl = di;
+                r_x = x;
+                r_pos = py * PW + px;
+                purpose = kEmigrate;
+            }
+            const uint2 key = run_key<!WHOLE>(p);
+            const uint4 w4 = philox4x32_10(make_uint4(0u, di, gen, purpose), key.x, key.y);
+            const uint32_t emig = word_below(w4.x, N) | ((w4.y >> 30) << 8);
+            if (around) {
+                r_draw = (emig >> 8) == need ? emig : 4u << 8;
+            } else if (purpose == kImmigrate) {
+                l_imm[at] = word_below(w4.x, N) | (word_below(w4.y, N) << 6) |
+                            (word_below(w4.z, N) << 12) | (word_below(w4.w, N) << 18);
+            } else if (purpose == kEmigrate) {
+                l_emig[at] = (uint16_t)emig;
+            } else {
+                // asynchronous ticks: an island runs a generation iff its
+                // activity draw is below the threshold; an idle island
+                // takes no immigrants and posts no emigrant
+                l_act[at] = w4.x < p.async_thr ? 1u : 0u;
+            }
+        }
+    };
+    if constexpr (KINDS != 0) draw_islands(0);
+    // the first generation's deposit
+    Deposit dep{{0u, 0u}, 0u};
+    if constexpr (!ASYNC) dep = scheduled_deposit(p, p.g);
+    // 2. stage the tile and its entries in LDS
     if (mine) {
         lds_store_lanes<APT>(l_trait + la0, tr);
         if (ASYNC) lds_store_lanes<APT>(l_count + la0, ct);
 #pragma unroll
         for (int w = 0; w < SW; ++w) lds_store_lanes<APT>(l_surf + w * TA + la0, sf[w]);
     }
-    __syncthreads();
-    if (MIGR) {
-        if (imm_take) {
-            // a neighbour delivers when its emigrant was sent our way
-            const uint32_t arrivals = (in_lo[0].x == 1u ? 1u : 0u) | (in_lo[1].x == 0u ? 2u : 0u) |
-                                      (in_lo[2].x == 3u ? 4u : 0u) | (in_lo[3].x == 2u ? 8u : 0u);
+    if constexpr (MIGR) {
+        for (uint32_t e = t; e < L.NE; e += blockDim.x) {
+            if (e != t) {
+                const uint32_t* o = p.ob_in + outbox_at(e);
+                in_lo = *reinterpret_cast<const uint4*>(o);
+                if (ASYNC && SW > 1) in_hi = *reinterpret_cast<const uint4*>(o + 4);
+            }
+            uint32_t* o = lds + L.entries + e * OBW;
+            *reinterpret_cast<uint4*>(o) = in_lo;
+            if (ASYNC && SW > 1) *reinterpret_cast<uint4*>(o + 4) = in_hi;
+        }
+    }
+    // the emigrants that come in from the islands around (an idle island
+    // of an asynchronous tick sends none)
+    RingBirth<SW, BM, ASYNC> rb;
+    uint32_t r_dir = r_draw >> 8;
+    if constexpr (MIGR && !WHOLE) {
+        if (r_dir < 4u) {
+            if constexpr (ASYNC)
+                if (philox4x32_10(make_uint4(0u, r_isl, p.g, kActivity), p.k0, p.k1).x >=
+                    p.async_thr)
+                    r_dir = 4u;
+            rb.load(p, r_isl, r_x, r_draw & 0xffu);
+        }
+    }
+    if constexpr (MIGR && !WHOLE) {
+        if (r_draw != kEmpty) {
+            uint32_t* o = lds + L.entries + (L.NE + r_pos) * OBW;
+            if (r_dir < 4u) post_entry<ASYNC>(o, rb.child(p, r_dir, dep));
+            else o[0] = 4u;
+        }
+    }
+    // the first generation's birth draws (float births' two blocks per agent
+    // would cost a wave per SIMD here: they are drawn after the barrier)
+    if constexpr (BM != kBirthFloat)
+        if (mine) draws.compute(run_key<!WHOLE>(p), j0, isl, p.g);
+    Children<SW, APT> kid;
+    uint32_t emig = 0;
+    auto advance = [&](uint32_t k) __attribute__((always_inline)) {
+        const uint32_t g = p.g + k;
+        __syncthreads();
+        const uint32_t half = (WHOLE ? k % p.tile.draws : k) * RI;
+        if constexpr (MIGR) {
+            // immigrants over the drawn slots (north, south, west, east: a
+            // later direction overwrites an earlier one)
+            if (k > 0 || p.has_inbox) {
+                // island ii is thread blockDim - 1 - ii's: a tile's last
+                // wavefronts, the first ones have made the islands' draws
+                // (worked out anew each generation: kept across the loop,
+                // the indices would cost a wave per SIMD)
+                const uint32_t wave0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)t);
+                uint32_t ii = blockDim.x - 1u - t;
+                bool take = false, some = blockDim.x - 64u - wave0 < RI;
+                if (own) {
+                    // the islands of this wavefront's agents
+                    ii = own * (wave0 >> 6) + (t & 63u);
+                    some = own * (wave0 >> 6) < RI;
+                }
+                asm volatile("" : "+v"(ii));
+                uint32_t iy = 0, ix = 0;
+                if (some) {
+                    iy = (ii * p.tile.w_magic) >> 20;
+                    ix = ii - iy * TW;
+                    take = ii < RI && ix < vw && iy < vh;
+                    if (own) take = take && (t & 63u) < own;
+                    if (ASYNC && take) take = l_act[half + ii] != 0u;
+                }
+                if (take) {
+                    const uint32_t* ent = lds + L.entries + ((k & 1u) ? L.NE * OBW : 0u);
+                    uint32_t n[4];
+                    if constexpr (WHOLE) {
 #pragma unroll
-            for (int d = 0; d < 4; ++d) {
-                if ((arrivals >> d) & 1u) {
-                    const uint32_t la = t * N + ((imm_slots >> (6 * d)) & 63u);
-                    l_trait[la] = in_lo[d].y;
-                    if constexpr (ASYNC) {
-                        l_count[la] = in_lo[d].z;
-                        l_surf[la] = in_lo[d].w;
-                        if (SW > 1) l_surf[TA + la] = in_hi[d].x;
+                        for (uint32_t d = 0; d < 4; ++d) n[d] = neighbour_of(ii, ix, d, W, RI);
                     } else {
-                        l_surf[la] = in_lo[d].z;
-                        if (SW > 1) l_surf[TA + la] = in_lo[d].w;
+                        const uint32_t c = (iy + 1u) * PW + ix + 1u;
+                        n[0] = c - PW;
+                        n[1] = c + PW;
+                        n[2] = c - 1u;
+                        n[3] = c + 1u;
+                    }
+                    const uint32_t slots = l_imm[half + ii];
+                    // all four entries at once: read one by one, each
+                    // would wait for the write before it
+                    uint4 o[4];
+                    uint32_t hi[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+                    for (uint32_t d = 0; d < 4; ++d) {
+                        o[d] = *reinterpret_cast<const uint4*>(ent + n[d] * OBW);
+                        if (ASYNC && SW > 1) hi[d] = ent[n[d] * OBW + 4u];
+                    }
+#pragma unroll
+                    for (uint32_t d = 0; d < 4; ++d) {
+                        // a neighbour delivers when its emigrant was sent our way
+                        if (o[d].x == (d ^ 1u)) {
+                            const uint32_t la = ii * N + ((slots >> (6u * d)) & 63u);
+                            l_trait[la] = o[d].y;
+                            if constexpr (ASYNC) l_count[la] = o[d].z;
+                            l_surf[la] = ASYNC ? o[d].w : o[d].z;
+                            if (SW > 1) l_surf[TA + la] = ASYNC ? hi[d] : o[d].w;
+                        }
                     }
                 }
+                if (own) wave_order();
+                else __syncthreads();
             }
         }
-        __syncthreads();
-    }
 
-    // 3. births (no barrier follows, so threads without agents may skip
-    // them; the resident form's next generation waits for every thread)
-    const uint32_t diff_mask = p.diff_log2 ? 0xffu : 1u;
+        // 3. births
+        if (mine) {
+            bool act = true;
+            if constexpr (ASYNC) {
+                act = l_act[half + il] != 0u;
+                if (!act) keep_agents<SW, APT>(lds, TA, la0, kid);
+            }
+            if (act) {
+                const uint32_t base = il * N;
+                // a wave-uniform choice between two copies of the births
+                if constexpr (BM == kBirthFloat) {
+                    uint2* wq = reinterpret_cast<uint2*>(lds + L.queue) + (t >> 6) * (64u * APT);
+                    if (n_shift)
+                        step_float_births<SW, APT, ASYNC, true>(p, lds, TA, base, j0, isl, g, dep,
+                                                                n_shift, wq, kid);
+                    else
+                        step_float_births<SW, APT, ASYNC, false>(p, lds, TA, base, j0, isl, g, dep,
+                                                                 n_shift, wq, kid);
+                } else if (n_shift) {
+                    step_births<SW, BM, APT, ASYNC, true>(p, lds, TA, base, draws, dep, n_shift,
+                                                          kid);
+                } else {
+                    step_births<SW, BM, APT, ASYNC, false>(p, lds, TA, base, draws, dep, n_shift,
+                                                           kid);
+                }
+            }
+            if constexpr (MIGR) {
+                emig = l_emig[half + il];
+                if (ASYNC && !act) emig = (emig & 0xffu) | (4u << 8);
+            }
+        }
+    };
+    // the island's emigrant, if it is one of this thread's agents
+    auto post = [&](uint32_t* o) __attribute__((always_inline)) {
+        const uint32_t qe = (emig & 0xffu) - j0;        // >= APT: another thread's
+        if (!mine || qe >= (uint32_t)APT) return;
+        Emigrant out{emig >> 8, kid.tr.v[0], ASYNC ? kid.cn.v[0] : 0u, kid.sf[0].v[0],
+                     SW > 1 ? kid.sf[SW - 1].v[0] : 0u};
+#pragma unroll
+        for (int q = 1; q < APT; ++q) {
+            const bool it = qe == (uint32_t)q;
+            const uint32_t a = kid.tr.v[q], b = kid.sf[0].v[q], c = kid.sf[SW - 1].v[q];
+            out.trait = it ? a : out.trait;
+            if constexpr (ASYNC) {
+                const uint32_t d = kid.cn.v[q];
+                out.counter = it ? d : out.counter;
+            }
+            out.s0 = it ? b : out.s0;
+            if (SW > 1) out.s1 = it ? c : out.s1;
+        }
+        post_entry<ASYNC>(o, out);
+    };
+    // the children of generation k are the next one's parents (every parent
+    // has been read), and the next generation's draws and deposit
+    auto succeed = [&](uint32_t k) __attribute__((always_inline)) {
+        if (own) wave_order();
+        else __syncthreads();
+        if constexpr (MIGR) post(lds + L.entries + (((k & 1u) ? 0u : L.NE) + eidx) * OBW);
+        if (mine) {
+            lds_store_lanes<APT>(l_trait + la0, kid.tr);
+            if constexpr (ASYNC) lds_store_lanes<APT>(l_count + la0, kid.cn);
+#pragma unroll
+            for (int w = 0; w < SW; ++w) lds_store_lanes<APT>(l_surf + w * TA + la0, kid.sf[w]);
+        }
+        if constexpr (WHOLE && KINDS != 0) {
+            if ((k + 1u) % p.tile.draws == 0u) {
+                // over draws that other wavefronts' births may still read
+                if (own) __syncthreads();
+                draw_islands(k + 1u);
+            }
+        }
+        if constexpr (!ASYNC) dep = scheduled_deposit(p, p.g + k + 1u);
+        if constexpr (BM != kBirthFloat) {
+            // (the slots' share of the first two rounds is worked out again:
+            // kept from the generation before, it would cost registers)
+            uint32_t j = j0;
+            asm volatile("" : "+v"(j));
+            if (mine) draws.compute(run_key<!WHOLE>(p), j, isl, p.g + k + 1u);
+        }
+    };
+    if constexpr (WHOLE || KINDS == 0) {
+        for (uint32_t k = 0;; ++k) {
+            advance(k);
+            if (k + 1u == p.gens) break;
+            succeed(k);
+        }
+    } else {
+        advance(0);
+        if (p.gens > 1u) {
+            succeed(0);
+            advance(1u);
+        }
+    }
+    if constexpr (MIGR) post(p.ob_out + (size_t)isl * OBW);
     if (mine) {
-        if constexpr (BM == kBirthFloat) draws.compute(p, j0, first_isl + il);
-        // draws onto [0, N): a shift when N is a power of two above 1 (a
-        // wave-uniform choice between two copies of the births)
-        const uint32_t n_shift =
-            (N > 1u && (N & (N - 1u)) == 0u) ? 32u - __builtin_ctz(N) : 0u;
-        if (n_shift)
-            step_births<SW, BM, MIGR, APT, ASYNC, true>(p, first_isl, la0, il, j0, draws,
-                                                        site_word, site_shift, diff_mask, n_shift);
-        else
-            step_births<SW, BM, MIGR, APT, ASYNC, false>(p, first_isl, la0, il, j0, draws,
-                                                         site_word, site_shift, diff_mask, n_shift);
+        store_lanes<APT>(p.out_trait, ga, kid.tr);
+        // a synchronous run keeps no counter plane: every counter is g + gens
+        if constexpr (ASYNC) store_lanes<APT>(p.out_counter, ga, kid.cn);
+#pragma unroll
+        for (int w = 0; w < SW; ++w) store_lanes<APT>(p.out_surf + w * A, ga, kid.sf[w]);
     }
 }
 
+// Float births are bound by VALU issue (98 % of it): registers for seven
+// wavefronts per SIMD instead of six are worth the few scalar spills that
+// they cost (float trial 112.0 -> 109.7 us per generation).
 template <int SW, uint32_t BM, bool MIGR, int APT, bool ASYNC>
-__global__ __launch_bounds__(1024) void step_kernel(const StepParams p) {
-    step_tile<SW, BM, MIGR, APT, ASYNC>(p, xcd_local_block(blockIdx.x, gridDim.x));
+__global__ __launch_bounds__(1024)
+__attribute__((amdgpu_waves_per_eu(BM == kBirthFloat && !ASYNC ? 7 : 1, 8)))
+void step_kernel(const StepParams p) {
+    step_tile<SW, BM, MIGR, APT, ASYNC, false>(p, xcd_local_block(blockIdx.x, gridDim.x));
 }
 
 // The resident form of a small synchronous run: its whole torus is one
-// tile, and one workgroup takes it through all gens generations of a launch
-// batch, with a workgroup barrier between generations where the plain form
-// has a kernel boundary.  A generation then costs neither a launch nor the
-// chip-wide cache write-back and invalidation between kernels, and its
-// planes and outboxes stay in this CU's caches.  p is generation p.g's;
-// sites holds the batch's schedule from ingest tau0.
+// tile, and one workgroup takes it through all p.gens generations of a
+// launch batch in LDS, with a workgroup barrier between generations where
+// the plain form has a kernel boundary.
 template <int SW, uint32_t BM, bool MIGR, int APT>
-__global__ __launch_bounds__(1024) void resident_step_kernel(StepParams p, const uint32_t gens,
-                                                            const uint32_t* __restrict__ sites,
-                                                            const uint32_t tau0) {
-    for (uint32_t k = 0; k < gens; ++k) {
-        if (k > 0) {
-            // the previous generation's children and emigrants are this
-            // one's parents and immigrants: every thread's stores and LDS
-            // reads are done before any thread loads or stages again
-            __syncthreads();
-            // the ping-pong buffers swap roles (the read side is typed const)
-            uint32_t* t = const_cast<uint32_t*>(p.in_trait);
-            p.in_trait = p.out_trait;
-            p.out_trait = t;
-            t = const_cast<uint32_t*>(p.in_surf);
-            p.in_surf = p.out_surf;
-            p.out_surf = t;
-            t = const_cast<uint32_t*>(p.ob_in);
-            p.ob_in = p.ob_out;
-            p.ob_out = t;
-            ++p.g;
-            p.has_inbox = MIGR ? 1u : 0u;
-            p.site = p.g % p.interval == 0u ? sites + (p.g / p.interval - tau0) : nullptr;
-        }
-        step_tile<SW, BM, MIGR, APT, false>(p, 0u);
-    }
+__global__ __launch_bounds__(1024) void resident_step_kernel(const StepParams p) {
+    step_tile<SW, BM, MIGR, APT, false, true>(p, 0u);
 }
 
-size_t step_lds_bytes(uint32_t tile_isl, uint32_t N, uint32_t SW) {
-    const size_t TA = ((size_t)tile_isl * N + 3) & ~(size_t)3;
-    return ((2 + SW) * TA + 2 * (size_t)tile_isl) * 4;
+size_t step_lds_bytes(const TileGeom& tg, uint32_t N, uint32_t SW, bool async,
+                      bool float_births, uint32_t apt) {
+    const bool whole = tg.whole != 0;
+    const uint32_t RI = tg.w * tg.h;
+    const TileLds l = tile_lds(RI, whole ? RI : (tg.w + 2u) * (tg.h + 2u), N, SW, async,
+                               tg.draws);
+    return 4 * (size_t)l.queue + (float_births ? 8 * (size_t)tg.threads * apt : 0);
 }
-
-size_t step_lds_bytes(uint32_t tile_isl, uint32_t N, uint32_t SW, bool float_births,
-                      uint32_t block_threads, uint32_t apt) {
-    const size_t b = step_lds_bytes(tile_isl, N, SW);
-    if (!float_births) return b;
-    return ((b + 15) & ~(size_t)15) + (size_t)block_threads * apt * 8;   // the draw queues
-}
-
-// rs.gens == 0: one generation over the run's tiles; otherwise the resident
-// form (rs.gens generations of a synchronous run that is one tile).
-struct Resident {
-    uint32_t gens;
-    const uint32_t* sites;
-    uint32_t tau0;
-};
 
 template <int SW, uint32_t BM, bool MIGR, int APT, bool ASYNC>
-static hipError_t launch_step_t(const StepParams& p, uint32_t block_threads, const Resident& rs,
-                                hipStream_t stream) {
-    if (p.tile_isl == 0 || p.tile_isl > block_threads) return hipErrorInvalidValue;
-    const uint32_t tiles = (p.I + p.tile_isl - 1) / p.tile_isl;
-    const size_t lds =
-        step_lds_bytes(p.tile_isl, p.N, SW, BM == kBirthFloat, block_threads, APT);
-    if (rs.gens) {
-        if constexpr (ASYNC) return hipErrorInvalidValue;
-        if (tiles != 1 || !rs.sites) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((resident_step_kernel<SW, BM, MIGR, APT>), dim3(1),
-                           dim3(block_threads), lds, stream, p, rs.gens, rs.sites, rs.tau0);
+static hipError_t launch_step_t(const StepParams& p, hipStream_t stream) {
+    const TileGeom& tg = p.tile;
+    if (p.gens == 0 || tg.w * tg.h * p.N > tg.threads * APT || tg.threads > 1024)
+        return hipErrorInvalidValue;
+    const size_t lds = step_lds_bytes(tg, p.N, SW, ASYNC, BM == kBirthFloat, APT);
+    if (tg.whole) {
+        if constexpr (ASYNC) {
+            return hipErrorInvalidValue;
+        } else {
+            if (tg.w != p.W || tg.h != p.H) return hipErrorInvalidValue;
+            hipLaunchKernelGGL((resident_step_kernel<SW, BM, MIGR, APT>), dim3(1),
+                               dim3(tg.threads), lds, stream, p);
+        }
     } else {
-        hipLaunchKernelGGL((step_kernel<SW, BM, MIGR, APT, ASYNC>), dim3(tiles),
-                           dim3(block_threads), lds, stream, p);
+        // more generations than the emigrants around a tile reach
+        if (p.gens > kTileGens && (MIGR || ASYNC)) return hipErrorInvalidValue;
+        if (2u * (tg.w + tg.h) > tg.threads) return hipErrorInvalidValue;
+        hipLaunchKernelGGL((step_kernel<SW, BM, MIGR, APT, ASYNC>), dim3(tg.cols * tg.rows),
+                           dim3(tg.threads), lds, stream, p);
     }
     return hipGetLastError();
 }
 
 template <int SW, uint32_t BM, bool MIGR, bool ASYNC>
-static hipError_t launch_step_apt(const StepParams& p, uint32_t apt, uint32_t block_threads,
-                                  const Resident& rs, hipStream_t stream) {
-    if (apt == 4) return launch_step_t<SW, BM, MIGR, 4, ASYNC>(p, block_threads, rs, stream);
-    if (apt == 2) return launch_step_t<SW, BM, MIGR, 2, ASYNC>(p, block_threads, rs, stream);
-    return launch_step_t<SW, BM, MIGR, 1, ASYNC>(p, block_threads, rs, stream);
+static hipError_t launch_step_apt(const StepParams& p, uint32_t apt, hipStream_t stream) {
+    if (apt == 4) return launch_step_t<SW, BM, MIGR, 4, ASYNC>(p, stream);
+    if (apt == 2) return launch_step_t<SW, BM, MIGR, 2, ASYNC>(p, stream);
+    return launch_step_t<SW, BM, MIGR, 1, ASYNC>(p, stream);
 }
 
 template <int SW, uint32_t BM, bool ASYNC>
 static hipError_t launch_step_mig(const StepParams& p, bool migration, uint32_t apt,
-                                  uint32_t block_threads, const Resident& rs,
                                   hipStream_t stream) {
-    return migration ? launch_step_apt<SW, BM, true, ASYNC>(p, apt, block_threads, rs, stream)
-                     : launch_step_apt<SW, BM, false, ASYNC>(p, apt, block_threads, rs, stream);
+    return migration ? launch_step_apt<SW, BM, true, ASYNC>(p, apt, stream)
+                     : launch_step_apt<SW, BM, false, ASYNC>(p, apt, stream);
 }
 
 template <int SW, bool ASYNC>
 static hipError_t launch_step_model(const StepParams& p, uint32_t birth_model, bool migration,
-                                    uint32_t apt, uint32_t block_threads, const Resident& rs,
-                                    hipStream_t stream) {
+                                    uint32_t apt, hipStream_t stream) {
     if (birth_model == kBirthFloat)
-        return launch_step_mig<SW, kBirthFloat, ASYNC>(p, migration, apt, block_threads, rs,
-                                                       stream);
+        return launch_step_mig<SW, kBirthFloat, ASYNC>(p, migration, apt, stream);
     if (birth_model == kBirthIntTournament)
-        return launch_step_mig<SW, kBirthIntTournament, ASYNC>(p, migration, apt, block_threads,
-                                                               rs, stream);
-    return launch_step_mig<SW, kBirthIntNeutral, ASYNC>(p, migration, apt, block_threads, rs,
-                                                        stream);
+        return launch_step_mig<SW, kBirthIntTournament, ASYNC>(p, migration, apt, stream);
+    return launch_step_mig<SW, kBirthIntNeutral, ASYNC>(p, migration, apt, stream);
 }
 
 template <bool ASYNC>
 static hipError_t launch_step_sw(const StepParams& p, uint32_t SW, uint32_t birth_model,
-                                 bool migration, uint32_t apt, uint32_t block_threads,
-                                 const Resident& rs, hipStream_t stream) {
-    if (SW == 1)
-        return launch_step_model<1, ASYNC>(p, birth_model, migration, apt, block_threads, rs,
-                                           stream);
-    return launch_step_model<2, ASYNC>(p, birth_model, migration, apt, block_threads, rs, stream);
+                                 bool migration, uint32_t apt, hipStream_t stream) {
+    if (SW == 1) return launch_step_model<1, ASYNC>(p, birth_model, migration, apt, stream);
+    return launch_step_model<2, ASYNC>(p, birth_model, migration, apt, stream);
 }
 
 hipError_t launch_step(const StepParams& p, uint32_t SW, uint32_t birth_model, bool migration,
-                       uint32_t agents_per_thread, uint32_t block_threads, hipStream_t stream) {
-    const Resident none{0u, nullptr, 0u};
+                       uint32_t agents_per_thread, hipStream_t stream) {
     if (p.async_thr)
-        return launch_step_sw<true>(p, SW, birth_model, migration, agents_per_thread,
-                                    block_threads, none, stream);
-    return launch_step_sw<false>(p, SW, birth_model, migration, agents_per_thread, block_threads,
-                                 none, stream);
-}
-
-hipError_t launch_resident_step(const StepParams& p, uint32_t gens, const uint32_t* sites,
-                                uint32_t tau0, uint32_t SW, uint32_t birth_model, bool migration,
-                                uint32_t agents_per_thread, uint32_t block_threads,
-                                hipStream_t stream) {
-    if (gens == 0) return hipSuccess;
-    if (p.async_thr) return hipErrorInvalidValue;
-    return launch_step_sw<false>(p, SW, birth_model, migration, agents_per_thread, block_threads,
-                                 Resident{gens, sites, tau0}, stream);
+        return launch_step_sw<true>(p, SW, birth_model, migration, agents_per_thread, stream);
+    return launch_step_sw<false>(p, SW, birth_model, migration, agents_per_thread, stream);
 }
 
 // ---------------------------------------------------------------------------
@@ -819,9 +1174,9 @@ hipError_t launch_batch_sites(const BatchRun* runs, uint32_t nruns, uint32_t max
 
 template <int SW, uint32_t BM, bool MIGR>
 __device__ __forceinline__ void step_tile_apt(const StepParams& p, uint32_t tile, uint32_t apt_log2) {
-    if (apt_log2 == 2) step_tile<SW, BM, MIGR, 4>(p, tile);
-    else if (apt_log2 == 1) step_tile<SW, BM, MIGR, 2>(p, tile);
-    else step_tile<SW, BM, MIGR, 1>(p, tile);
+    if (apt_log2 == 2) step_tile<SW, BM, MIGR, 4, false, false>(p, tile);
+    else if (apt_log2 == 1) step_tile<SW, BM, MIGR, 2, false, false>(p, tile);
+    else step_tile<SW, BM, MIGR, 1, false, false>(p, tile);
 }
 
 template <uint32_t BM>
@@ -869,34 +1224,32 @@ __global__ __launch_bounds__(1024) void batch_step_kernel(const BatchRun* __rest
     const uint32_t lo = before - 1u;       // pre[0] = 0: at least one run
     const BatchRun& R = runs[lo];
     const uint32_t t = xcd_tab[(kXcds + x) * nruns + lo] + (j - pre[lo]);
-    if (k >= R.gens) return;
-    const uint32_t g = R.T0 + k;
-    const uint32_t src = g & 1u, dst = (g + 1u) & 1u;
+    if (k * kTileGens >= R.gens) return;
+    const uint32_t g = R.T0 + k * kTileGens;
+    const uint32_t src = k & 1u, dst = src ^ 1u;
     StepParams p;
     p.in_trait = R.trait[src];
-    p.in_counter = R.counter[src];
+    p.in_counter = nullptr;    // batched runs are synchronous
     p.in_surf = R.surf[src];
     p.out_trait = R.trait[dst];
-    p.out_counter = R.counter[dst];
+    p.out_counter = nullptr;
     p.out_surf = R.surf[dst];
     p.ob_in = R.outbox[src];
     p.ob_out = R.outbox[dst];
-    // deposit iff g is a multiple of the interval; its site is entry
-    // g / interval - tau0 of this batch's schedule
-    p.site = g % R.interval == 0 ? R.sites + (g / R.interval - ingests_of(R.T0, R.interval))
-                                 : nullptr;
+    p.sites = R.sites;
+    p.tau0 = ingests_of(R.T0, R.interval);
     p.diff_log2 = R.diff_log2;
-    p.W = R.W; p.H = R.H; p.N = R.N; p.I = R.I; p.A = R.A;
+    p.W = R.W; p.H = R.H; p.N = R.N;
+    p.I = R.W * R.H;
+    p.A = p.I * R.N;
     p.g = g;
+    p.gens = min(kTileGens, R.gens - k * kTileGens);
     p.k0 = R.k0; p.k1 = R.k1;
     p.mut_thr = R.mut_thr; p.mut_lo = R.mut_lo; p.mut_span = R.mut_span;
     const bool mig = (R.variant >> 3) & 1u;
     p.has_inbox = (mig && g > 0) ? 1u : 0u;
-    p.tile_isl = R.tile_isl;
-    p.div_magic = R.div_magic;
-    p.w_magic = R.w_magic;
-    p.w_shift = R.w_shift;
-    p.async_thr = 0u;          // batched runs are synchronous
+    p.tile = R.tile;
+    p.async_thr = 0u;
     p.rules = nullptr;
     p.ring = nullptr;
     p.ring_lo = 0u;
@@ -905,7 +1258,7 @@ __global__ __launch_bounds__(1024) void batch_step_kernel(const BatchRun* __rest
     p.interval = R.interval;
     p.tour = R.tour;
     p.del_thr = R.del_thr; p.ben_thr = R.ben_thr;
-    p.del_sigma = R.del_sigma; p.ben_sigma = R.ben_sigma;
+    p.del_scale = -(double)R.del_sigma; p.ben_scale = R.ben_sigma;
     const uint32_t model = (R.variant >> 1) & 3u;
     if (model == kBirthIntTournament) step_tile_variant<kBirthIntTournament>(p, t, R.variant);
     else if (WITH_FLOAT && model == kBirthFloat) step_tile_variant<kBirthFloat>(p, t, R.variant);

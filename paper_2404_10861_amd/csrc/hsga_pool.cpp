@@ -57,11 +57,11 @@ struct Group {
 // One advance's launches (a group may be empty).
 struct GraphKey {
     Group grp[kGroups];
-    uint32_t gens = 0, block = 0;
+    uint32_t gens = 0, launches = 0, block = 0;
     bool operator==(const GraphKey& o) const {
         for (uint32_t q = 0; q < kGroups; ++q)
             if (!(grp[q] == o.grp[q])) return false;
-        return gens == o.gens && block == o.block;
+        return gens == o.gens && launches == o.launches && block == o.block;
     }
 };
 
@@ -157,6 +157,9 @@ void release_handles(ga_pool* p) {
 // surface words, in and out (the balance of the launch groups)
 uint64_t words_per_generation(const ga_run& r) { return (uint64_t)r.A * (1 + r.SW); }
 
+// launches that take a run through g generations
+uint32_t launches_of(uint32_t g) { return (g + hsga::kTileGens - 1) / hsga::kTileGens; }
+
 uint32_t variant_of(const ga_run& r) {
     uint32_t v = 0;
     if (r.SW == 2) v |= 1u;
@@ -181,7 +184,7 @@ int capture_group(ga_pool* p, const GraphKey& key, uint32_t q) {
     hipError_t e = hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return hip_fail(e, "hipStreamBeginCapture");
     hipError_t le = hipSuccess;
-    for (uint32_t k = 0; k < key.gens && le == hipSuccess; ++k) le = launch_group(p, key, q, k);
+    for (uint32_t k = 0; k < key.launches && le == hipSuccess; ++k) le = launch_group(p, key, q, k);
     hipGraph_t graph = nullptr;
     e = hipStreamEndCapture(s, &graph);
     if (le == hipSuccess && e == hipSuccess)
@@ -234,7 +237,7 @@ int enqueue_launches(ga_pool* p, const GraphKey& key) {
         for (uint32_t q = 0; q < kGroups && le == hipSuccess; ++q)
             if (key.grp[q].count) le = hipGraphLaunch(p->exec[q], stream_of(p, q));
     } else {
-        for (uint32_t k = 0; k < key.gens && le == hipSuccess; ++k)
+        for (uint32_t k = 0; k < key.launches && le == hipSuccess; ++k)
             for (uint32_t q = 0; q < kGroups && le == hipSuccess; ++q)
                 if (key.grp[q].count) le = launch_group(p, key, q, k);
     }
@@ -401,22 +404,21 @@ int ga_pool_advance(ga_pool* p, uint32_t max_gens, uint32_t* gens_enqueued) {
         Group& grp = key.grp[q];
         r.block = p->block;
         const uint32_t g = std::min(G, s.target - r.T);
-        const hsga::StepParams sp =
-            step_params(&r, r.T, hsga::ingests_of(r.T, r.cfg.ingest_interval));
-        // the island pass takes one island per thread
-        if (sp.tile_isl == 0 || sp.tile_isl > p->block)
-            return fail(GA_EINVAL, "tile has more islands than the workgroup has threads");
+        hsga::TileGeom tile = run_tile(&r, p->block);
+        tile.threads = (uint16_t)p->block;
+        const hsga::StepParams sp = step_params(
+            &r, r.T, g, r.cur, hsga::ingests_of(r.T, r.cfg.ingest_interval), tile);
         hsga::BatchRun& b = p->h_table[i];
-        for (int j = 0; j < 2; ++j) {
-            b.trait[j] = r.trait[j];
-            b.counter[j] = r.counter[j];
-            b.surf[j] = r.surf[j];
-            b.outbox[j] = r.outbox[j];
+        for (uint32_t j = 0; j < 2; ++j) {
+            const uint32_t c = r.cur ^ j;
+            b.trait[j] = r.trait[c];
+            b.surf[j] = r.surf[c];
+            b.outbox[j] = r.outbox[c];
         }
         b.sites = r.sites;
         b.layout = r.layout;
         b.rules = r.rules;
-        b.W = sp.W; b.H = sp.H; b.N = sp.N; b.I = sp.I; b.A = sp.A;
+        b.W = sp.W; b.H = sp.H; b.N = sp.N;
         b.T0 = r.T;
         b.gens = g;
         b.k0 = sp.k0; b.k1 = sp.k1;
@@ -427,21 +429,19 @@ int ga_pool_advance(ga_pool* p, uint32_t max_gens, uint32_t* gens_enqueued) {
         grp.with_float = grp.with_float || birth_model(r.cfg) == hsga::kBirthFloat;
         b.tour = sp.tour;
         b.del_thr = sp.del_thr; b.ben_thr = sp.ben_thr;
-        b.del_sigma = sp.del_sigma; b.ben_sigma = sp.ben_sigma;
+        b.del_sigma = r.cfg.del_sigma; b.ben_sigma = r.cfg.ben_sigma;
         b.interval = r.cfg.ingest_interval;
         b.diff_log2 = sp.diff_log2;
-        b.tile_isl = sp.tile_isl;
-        b.div_magic = sp.div_magic;
-        b.w_magic = sp.w_magic;
-        b.w_shift = sp.w_shift;
-        const uint32_t rt = (r.I + sp.tile_isl - 1) / sp.tile_isl;
+        b.tile = tile;
+        const uint32_t rt = tile.cols * tile.rows;
         run_tiles[i] = rt;
         grp.tiles += rt;
         ++grp.count;
         key.gens = std::max(key.gens, g);
-        grp.lds = std::max(grp.lds, hsga::step_lds_bytes(sp.tile_isl, r.N, r.SW,
+        key.launches = std::max(key.launches, launches_of(g));
+        grp.lds = std::max(grp.lds, hsga::step_lds_bytes(tile, r.N, r.SW, false,
                                                          birth_model(r.cfg) == hsga::kBirthFloat,
-                                                         p->block, r.apt));
+                                                         r.apt));
     }
     // each group's xcd table, group after group
     uint32_t first = 0;
@@ -475,6 +475,7 @@ int ga_pool_advance(ga_pool* p, uint32_t max_gens, uint32_t* gens_enqueued) {
     for (uint32_t i = 0; i < nruns; ++i) {
         Slot& s = p->slots[active[i]];
         s.run.T += p->h_table[i].gens;
+        s.run.cur ^= launches_of(p->h_table[i].gens) & 1u;
     }
     if (gens_enqueued) *gens_enqueued = key.gens;
     return GA_OK;

@@ -35,9 +35,64 @@ __global__ __launch_bounds__(256) void sample_kernel(const uint32_t* __restrict_
     for (uint32_t w = 0; w < SW; ++w) surf_out[(size_t)k * SW + w] = surf[(size_t)w * A + a];
 }
 
+// The whole population as its sample, four agents per thread: plain copies,
+// transposed where a surface has two words, so bound by memory; 16-byte
+// accesses move every line once, where one agent per thread wrote the two
+// words of a surface in two strided passes.
+template <int SW, bool COUNTER>
+__global__ __launch_bounds__(256) void sample_all_kernel(const uint4* __restrict__ counter,
+                                                        const uint32_t* __restrict__ surf,
+                                                        uint32_t A, uint32_t T,
+                                                        uint4* __restrict__ idx_out,
+                                                        uint4* __restrict__ counter_out,
+                                                        uint4* __restrict__ surf_out) {
+    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= A / 4u) return;
+    const uint4 lo = reinterpret_cast<const uint4*>(surf)[i];
+    uint4 hi = lo, c = make_uint4(T, T, T, T);
+    if constexpr (SW > 1) hi = reinterpret_cast<const uint4*>(surf + A)[i];
+    if constexpr (COUNTER) c = counter[i];
+    idx_out[i] = make_uint4(4u * i, 4u * i + 1u, 4u * i + 2u, 4u * i + 3u);
+    counter_out[i] = c;
+    if constexpr (SW > 1) {
+        surf_out[2 * (size_t)i] = make_uint4(lo.x, hi.x, lo.y, hi.y);
+        surf_out[2 * (size_t)i + 1] = make_uint4(lo.z, hi.z, lo.w, hi.w);
+    } else {
+        surf_out[i] = lo;
+    }
+}
+
+template <int SW>
+static void launch_sample_all(const uint32_t* counter, const uint32_t* surf, uint32_t A,
+                              uint32_t T, uint32_t* idx_out, uint32_t* counter_out,
+                              uint32_t* surf_out, hipStream_t stream) {
+    const dim3 blocks((A / 4 + 255) / 256);
+    auto* c = reinterpret_cast<const uint4*>(counter);
+    auto* io = reinterpret_cast<uint4*>(idx_out);
+    auto* co = reinterpret_cast<uint4*>(counter_out);
+    auto* so = reinterpret_cast<uint4*>(surf_out);
+    if (counter)
+        hipLaunchKernelGGL((sample_all_kernel<SW, true>), blocks, dim3(256), 0, stream, c, surf, A,
+                           T, io, co, so);
+    else
+        hipLaunchKernelGGL((sample_all_kernel<SW, false>), blocks, dim3(256), 0, stream, c, surf,
+                           A, T, io, co, so);
+}
+
 hipError_t launch_sample(const uint32_t* counter, const uint32_t* surf, uint32_t A, uint32_t SW,
                          uint32_t n, uint32_t T, uint32_t k0, uint32_t k1, uint32_t* idx_out,
                          uint32_t* counter_out, uint32_t* surf_out, hipStream_t stream) {
+    // whole words of four agents where planes and buffers allow it (the
+    // planes' own starts are 256-byte aligned, the second word's is A words on)
+    const uintptr_t at = (uintptr_t)idx_out | (uintptr_t)counter_out | (uintptr_t)surf_out |
+                         (uintptr_t)surf | (uintptr_t)counter;
+    if (A <= n && A % 4 == 0 && at % 16 == 0) {
+        if (SW == 1)
+            launch_sample_all<1>(counter, surf, A, T, idx_out, counter_out, surf_out, stream);
+        else
+            launch_sample_all<2>(counter, surf, A, T, idx_out, counter_out, surf_out, stream);
+        return hipGetLastError();
+    }
     const uint32_t taken = A <= n ? A : n;
     const uint32_t blocks = (taken + 255) / 256;
     hipLaunchKernelGGL(sample_kernel, dim3(blocks ? blocks : 1), dim3(256), 0, stream, counter,
