@@ -529,15 +529,15 @@ __global__ __launch_bounds__(256) void phylo_keys_kernel(uint32_t n, uint32_t np
     idx[i] = i < n ? i : 0xffffffffu;
 }
 
-// Bitonic sort of (key, index) over npad (a power of two) entries, ascending
-// by key then index.  The network is the usual one: for k = 2, 4, .., npad
-// and j = k/2, .., 1, entries i and i + j (i with bit j clear) are ordered
-// ascending where bit k of i is clear and descending where it is set.
-// Stages with j < kSortChunk stay inside aligned chunks of kSortChunk
-// entries, so each workgroup runs them in LDS: all stages of k <= the chunk
-// at once (phylo_sort_local_kernel), and for each larger k its strides
-// below the chunk after the strides at or above it, which take one launch
-// each over the whole array (phylo_sort_global_kernel).
+// Sort of (key, index), ascending by key then index.  Chunks of kSortChunk
+// entries are sorted in LDS by a bitonic network (for k = 2, 4, .., chunk
+// and j = k/2, .., 1, entries i and i + j, i with bit j clear, are ordered
+// ascending where bit k of i is clear and descending where it is set), then
+// merged in one launch: an entry's place is its place in its own chunk plus
+// the number of entries before it in each other one, a binary search each.
+// A chain of 11 loads per search (several searches side by side) replaces
+// the network's passes over the whole array, one launch per stride: the
+// 10,000-annotation tree took nine launches after the chunks' sort.
 constexpr uint32_t kSortChunk = 2048;
 
 __device__ __forceinline__ void sort_exchange(uint64_t& ka, uint32_t& ia, uint64_t& kb,
@@ -554,10 +554,9 @@ __device__ __forceinline__ void sort_exchange(uint64_t& ka, uint32_t& ia, uint64
 }
 
 // One chunk of `chunk` entries (a power of two, at most kSortChunk) per
-// workgroup of chunk / 2 threads.  k_only = 0: every stage with k <= chunk;
-// otherwise the stages j = chunk/2 .. 1 of k = k_only.
+// workgroup of chunk / 2 threads.
 __global__ __launch_bounds__(kSortChunk / 2) void phylo_sort_local_kernel(
-    uint32_t chunk, uint32_t k_only, const uint32_t* __restrict__ ws, uint64_t* __restrict__ keys,
+    uint32_t chunk, const uint32_t* __restrict__ ws, uint64_t* __restrict__ keys,
     uint32_t* __restrict__ idx) {
     if (ws[kWsStatus] != 0) return;
     __shared__ uint64_t sk[kSortChunk];
@@ -569,13 +568,10 @@ __global__ __launch_bounds__(kSortChunk / 2) void phylo_sort_local_kernel(
     sk[t + chunk / 2] = keys[base + t + chunk / 2];
     si[t + chunk / 2] = idx[base + t + chunk / 2];
     __syncthreads();
-    const uint32_t k_first = k_only ? k_only : 2u;
-    const uint32_t k_last = k_only ? k_only : chunk;
-    for (uint32_t k = k_first; k <= k_last; k <<= 1) {
-        for (uint32_t j = (k_only ? chunk : k) >> 1; j > 0; j >>= 1) {
+    for (uint32_t k = 2; k <= chunk; k <<= 1) {
+        for (uint32_t j = k >> 1; j > 0; j >>= 1) {
             const uint32_t i = (t / j) * 2 * j + (t % j);
-            const bool up = ((base + i) & k) == 0;
-            sort_exchange(sk[i], si[i], sk[i + j], si[i + j], up);
+            sort_exchange(sk[i], si[i], sk[i + j], si[i + j], (i & k) == 0);
             __syncthreads();
         }
     }
@@ -585,39 +581,38 @@ __global__ __launch_bounds__(kSortChunk / 2) void phylo_sort_local_kernel(
     idx[base + t + chunk / 2] = si[t + chunk / 2];
 }
 
-// Stage (k, j) over the whole array, one pair per thread (npad / 2 threads).
-__global__ __launch_bounds__(256) void phylo_sort_global_kernel(uint32_t npad, uint32_t k,
-                                                                uint32_t j,
-                                                                const uint32_t* __restrict__ ws,
-                                                                uint64_t* __restrict__ keys,
-                                                                uint32_t* __restrict__ idx) {
+// The sorted chunks (kSortChunk entries each) merged into the first n places
+// of keys_out and idx_out; the padding, greater than every annotation's
+// entry, is left out.
+__global__ __launch_bounds__(256) void phylo_merge_kernel(uint32_t n, uint32_t chunks,
+                                                         const uint32_t* __restrict__ ws,
+                                                         const uint64_t* __restrict__ keys,
+                                                         const uint32_t* __restrict__ idx,
+                                                         uint64_t* __restrict__ keys_out,
+                                                         uint32_t* __restrict__ idx_out) {
     if (ws[kWsStatus] != 0) return;
-    const uint32_t t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= npad / 2) return;
-    const uint32_t i = (t / j) * 2 * j + (t % j);
-    const uint32_t l = i + j;
-    uint64_t ki = keys[i], kl = keys[l];
-    uint32_t ii = idx[i], il = idx[l];
-    sort_exchange(ki, ii, kl, il, (i & k) == 0);
-    keys[i] = ki;
-    keys[l] = kl;
-    idx[i] = ii;
-    idx[l] = il;
-}
-
-void launch_phylo_sort(uint32_t npad, const uint32_t* ws, uint64_t* keys, uint32_t* idx,
-                       hipStream_t stream) {
-    if (npad < 2) return;
-    const uint32_t chunk = npad < kSortChunk ? npad : kSortChunk;
-    const uint32_t chunks = npad / chunk;
-    hipLaunchKernelGGL(phylo_sort_local_kernel, dim3(chunks), dim3(chunk / 2), 0, stream, chunk,
-                       0u, ws, keys, idx);
-    for (uint32_t k = 2 * chunk; k <= npad; k <<= 1) {
-        for (uint32_t j = k >> 1; j >= chunk; j >>= 1)
-            hipLaunchKernelGGL(phylo_sort_global_kernel, dim3((npad / 2 + 255) / 256), dim3(256),
-                               0, stream, npad, k, j, ws, keys, idx);
-        hipLaunchKernelGGL(phylo_sort_local_kernel, dim3(chunks), dim3(chunk / 2), 0, stream,
-                           chunk, k, ws, keys, idx);
+    const uint32_t e = blockIdx.x * blockDim.x + threadIdx.x;
+    if (e >= chunks * kSortChunk) return;
+    const uint64_t key = keys[e];
+    const uint32_t id = idx[e];
+    const uint32_t mine = e / kSortChunk;
+    uint32_t place = e % kSortChunk;
+    auto before = [&](uint32_t at) {
+        const uint64_t k = keys[at];
+        return k < key || (k == key && idx[at] < id);
+    };
+#pragma unroll 4
+    for (uint32_t c = 0; c < chunks; ++c) {
+        const uint32_t base = c * kSortChunk;
+        uint32_t lo = 0;                       // entries known to come before
+        for (uint32_t step = kSortChunk / 2; step > 0; step >>= 1)
+            if (before(base + lo + step - 1)) lo += step;
+        if (before(base + lo)) ++lo;
+        place += c == mine ? 0u : lo;
+    }
+    if (place < n) {
+        keys_out[place] = key;
+        idx_out[place] = id;
     }
 }
 
@@ -637,38 +632,77 @@ __device__ __forceinline__ uint64_t phylo_tau(const uint32_t* ws, uint32_t d) {
     return d < F ? (uint64_t)ws[kWsTimes + d] : (uint64_t)ws[kWsT];
 }
 
+// The boundaries' depths (level 0) and the table's levels up to
+// kTileLevels, a tile of 2^kTileLevels boundaries per workgroup: its depths
+// and those of the next tile are enough, and stay in LDS from level to
+// level, where each level was a launch of its own.
+constexpr uint32_t kTileLevels = 10;
+constexpr uint32_t kTableTile = 1u << kTileLevels;
 __global__ __launch_bounds__(256) void phylo_depth_kernel(uint32_t n, uint32_t diff_log2,
+                                                         uint32_t levels,
                                                          const uint32_t* __restrict__ ws,
                                                          const uint64_t* __restrict__ keys,
-                                                         uint8_t* __restrict__ depth,
+                                                         uint8_t* __restrict__ tab,
                                                          PhyloAcc* __restrict__ acc) {
     if (ws[kWsStatus] != 0) return;
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    const uint32_t F = ws[kWsF];
-    if (i == 0) {
+    constexpr uint32_t PER = 2 * kTableTile / 256;
+    __shared__ uint8_t low[2 * kTableTile];
+    const uint32_t t = threadIdx.x, first = blockIdx.x * kTableTile;
+    const uint32_t F = ws[kWsF], m = n - 1;
+    if (first + t == 0) {
         acc->sbl = 0;
         acc->pairs = 0;
         acc->internal = 0;
         acc->dmin = F;
     }
-    if (i + 1 < n) {
-        const uint64_t x = keys[i] ^ keys[i + 1];
-        const uint32_t d = x ? ((uint32_t)__clzll((long long)x) >> diff_log2) : 64u;
-        depth[i] = (uint8_t)(d < F ? d : F);
+    uint8_t v[PER];
+#pragma unroll
+    for (uint32_t q = 0; q < PER; ++q) {
+        const uint32_t i = t + 256u * q, b = first + i;
+        v[q] = 0xff;
+        if (b < m) {
+            const uint64_t x = keys[b] ^ keys[b + 1];
+            const uint32_t d = x ? ((uint32_t)__clzll((long long)x) >> diff_log2) : 64u;
+            v[q] = (uint8_t)(d < F ? d : F);
+            if (i < kTableTile) tab[b] = v[q];
+        }
+        low[i] = v[q];
+    }
+    for (uint32_t k = 1; k < levels && k <= kTileLevels; ++k) {
+        const uint32_t half = 1u << (k - 1);
+        __syncthreads();
+#pragma unroll
+        for (uint32_t q = 0; q < PER; ++q) {
+            const uint32_t i = t + 256u * q + half;
+            const uint8_t o = i < 2 * kTableTile ? low[i] : (uint8_t)0xff;
+            v[q] = o < v[q] ? o : v[q];
+        }
+        __syncthreads();
+#pragma unroll
+        for (uint32_t q = 0; q < PER; ++q) {
+            const uint32_t i = t + 256u * q, b = first + i;
+            low[i] = v[q];
+            if (i < kTableTile && b + 2 * half <= m) tab[(size_t)k * m + b] = v[q];
+        }
     }
 }
 
-// Level k of the sparse table from level k - 1 (m boundaries per level).
-__global__ __launch_bounds__(256) void phylo_table_kernel(uint32_t m, uint32_t k,
+// The levels above: minima of level kTileLevels at strides of its span.
+__global__ __launch_bounds__(256) void phylo_table_kernel(uint32_t m, uint32_t levels,
                                                          const uint32_t* __restrict__ ws,
                                                          uint8_t* __restrict__ tab) {
     if (ws[kWsStatus] != 0) return;
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    const uint32_t half = 1u << (k - 1);
-    if (i + 2 * half > m) return;
-    const uint8_t* prev = tab + (size_t)(k - 1) * m;
-    const uint8_t a = prev[i], b = prev[i + half];
-    tab[(size_t)k * m + i] = a < b ? a : b;
+    if (i + 2 * kTableTile > m) return;
+    const uint8_t* span = tab + (size_t)kTileLevels * m + i;
+    uint8_t v = span[0];
+    for (uint32_t k = kTileLevels + 1, j = 1; k < levels && i + (1u << k) <= m; ++k) {
+        for (; j < 1u << (k - kTileLevels); ++j) {
+            const uint8_t o = span[j * kTableTile];
+            v = o < v ? o : v;
+        }
+        tab[(size_t)k * m + i] = v;
+    }
 }
 
 // Nearest boundary i < b with depth[i] < d.
@@ -903,11 +937,28 @@ hipError_t launch_phylo(const Scheme& scm, uint32_t n, const uint32_t* counter,
                        surf, ws, ranked);
     hipLaunchKernelGGL(phylo_keys_kernel, dim3((uint32_t)((npad + 255) / 256)), dim3(256), 0,
                        stream, n, (uint32_t)npad, diff_log2, ranked, ws, keys, idx);
-    launch_phylo_sort((uint32_t)npad, ws, keys, idx, stream);
-    hipLaunchKernelGGL(phylo_depth_kernel, dim3(gn), dim3(256), 0, stream, n, diff_log2, ws, keys,
-                       tab, acc);
-    for (uint32_t k = 1; k < levels; ++k)
-        hipLaunchKernelGGL(phylo_table_kernel, dim3(gn), dim3(256), 0, stream, m, k, ws, tab);
+    if (npad > 1) {
+        const uint32_t chunk = npad < kSortChunk ? (uint32_t)npad : kSortChunk;
+        const uint32_t chunks = (n + chunk - 1) / chunk;
+        hipLaunchKernelGGL(phylo_sort_local_kernel, dim3(chunks), dim3(chunk / 2), 0, stream,
+                           chunk, ws, keys, idx);
+        if (chunks > 1) {
+            // into the workspace's layouts, which this query does not use
+            // (12 bytes per annotation of at least 20)
+            uint8_t* to = base + MrcaWorkspace::kHeader + (((size_t)n * 8 + 255) & ~(size_t)255);
+            uint64_t* keys_out = reinterpret_cast<uint64_t*>(to);
+            uint32_t* idx_out = reinterpret_cast<uint32_t*>(to + (size_t)n * 8);
+            hipLaunchKernelGGL(phylo_merge_kernel, dim3(chunks * kSortChunk / 256), dim3(256), 0,
+                               stream, n, chunks, ws, keys, idx, keys_out, idx_out);
+            keys = keys_out;
+            idx = idx_out;
+        }
+    }
+    const uint32_t tiles = m ? (m + kTableTile - 1) / kTableTile : 1u;
+    hipLaunchKernelGGL(phylo_depth_kernel, dim3(tiles), dim3(256), 0, stream, n, diff_log2, levels,
+                       ws, keys, tab, acc);
+    if (levels > kTileLevels + 1)
+        hipLaunchKernelGGL(phylo_table_kernel, dim3(gn), dim3(256), 0, stream, m, levels, ws, tab);
     if (m > 0)
         hipLaunchKernelGGL(phylo_boundary_kernel, dim3((m + 255) / 256), dim3(256), 0, stream, m,
                            levels, ws, tab, acc);
