@@ -9,9 +9,9 @@ are generated on the device; the paper's workloads are synthetic too).
 
 Prints one JSON line:
   value     agent-replications/s over the timed steps (births only)
-  roofline  the step kernel's algorithmic HBM bytes per launch (what a
-            synchronous generation must move) over its average launch
-            duration (HIP events on the run's stream);
+  roofline  the step kernel's algorithmic HBM bytes per launch (what two
+            synchronous generations staged on the chip must move) over its
+            average launch duration (HIP events on the run's stream);
             traffic: the HBM bytes per launch that rocprofv3 counted for
             the same code (profiles/), null once the code has changed
   cpu_baseline  the plain C oracle on a bounded sample of the same
@@ -42,8 +42,14 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "step_kernel_c2_traffic.json")
 SQ_FILE = os.path.join(ROOT, "profiles", "step_kernel_c2_sq_counters.json")
 
 
+# generations of one step launch: the population is read and written once
+# for both
+GENS_PER_LAUNCH = 2
+
+
 def algorithmic_bytes_per_generation(spec) -> int:
-    """The bytes one synchronous generation has to move: the trait and
+    """The bytes one synchronous generation has to move if it is a launch of
+    its own, and so what a launch of GENS_PER_LAUNCH moves: the trait and
     surface words of every parent read and of every child written (a
     record of 4 + S/8 bytes: every counter is the generation number, so
     none is stored), and each island's 16-byte migrant entry (direction,
@@ -363,7 +369,7 @@ def main(argv=None) -> int:
             copy_gbs = attainable_copy_gbs(torch, hs, dev, stream)
             res = benchmarks.batched_vs_plain(specs, dev, stream, tune=not args.batch_block,
                                               block_threads=args.batch_block or 256)
-            bytes_gen = sum(batch_bytes_per_generation(sp) for sp in specs)
+            bytes_gen = sum(batch_bytes_per_generation(sp) for sp in specs) / GENS_PER_LAUNCH
             res["algorithmic_bytes_per_generation"] = bytes_gen
             res["attainable_copy_GBs"] = copy_gbs
             gen_us = res["steady_generation_us"]
@@ -450,7 +456,8 @@ def main(argv=None) -> int:
     value = reps / elapsed
     bytes_per_launch = algorithmic_bytes_per_generation(spec)
     record_bytes = record_model_bytes_per_generation(spec)
-    avg_launch_s = kern_ms / 1000.0 / max(launches, 1)
+    # the step's events count generations
+    avg_launch_s = kern_ms / 1000.0 / max(launches, 1) * GENS_PER_LAUNCH
     achieved_gbs = bytes_per_launch / avg_launch_s / 1e9
     traffic = measured_traffic(spec)
     line = {
@@ -485,15 +492,18 @@ def main(argv=None) -> int:
             "frac": achieved_gbs / HBM_PEAK_GBS,
             "traffic": traffic,
             "kernel": "step_kernel<2, kBirthIntTournament, migration, 4 agents per thread>",
+            "generations_per_launch": GENS_PER_LAUNCH,
             "avg_launch_us": avg_launch_s * 1e6,
             "algorithmic_bytes_per_launch": bytes_per_launch,
-            "bytes_per_replication": bytes_per_launch / spec.agents,
+            "bytes_per_replication": bytes_per_launch / spec.agents / GENS_PER_LAUNCH,
             "attainable_copy_GBs": copy_gbs,
             "frac_of_attainable": achieved_gbs / copy_gbs,
             "note": "algorithmic bytes: 12-byte records (trait, 64 one-bit sites; every "
                     "counter is the generation number) read and written, and one 16-byte "
-                    "migrant entry written and read per island; record_model_* prices a "
-                    "stored counter and 32-byte entries, which this step does not move",
+                    "migrant entry written and read per island, once for the two "
+                    "generations of a launch (VALU issue, not bandwidth, is then the nearer "
+                    "bound); record_model_* prices a stored counter and 32-byte entries, "
+                    "which this step does not move",
             "record_model_bytes_per_launch": record_bytes,
             "record_model_GBs": record_bytes / avg_launch_s / 1e9,
             "traffic_GBs": traffic / avg_launch_s / 1e9 if traffic else None,

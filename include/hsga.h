@@ -597,12 +597,11 @@ int ga_probe_copy(const void *src, void *dst, size_t bytes, void *hip_stream);
 /* Launch shape of the step kernel: threads per workgroup (multiple of 64,
  * 64..1024) and agents per thread (1, 2 or 4; must divide pop_per_island;
  * 4 gives 16-byte population loads and stores).  A workgroup handles a
- * tile of block_threads * agents_per_thread / N whole islands staged in
- * LDS (at most 64 KiB).  0 keeps the current value.  Results do not depend
- * on the shape.  A run starts at 4 agents per thread when N allows, with
- * 64 threads for synchronous integer births on two-word surfaces, 128 for
- * integer births on one-word surfaces or in asynchronous ticks, and 256
- * for float births.
+ * tile of at most block_threads * agents_per_thread / N whole islands
+ * (256 at most), staged in LDS (at most 64 KiB), for two generations per
+ * launch; the library chooses the tile's sides.  0 keeps the current
+ * value.  Results do not depend on the shape.  A run starts at 4 agents
+ * per thread when N allows, with 256 threads.
  * Errors: GA_EINVAL.                                                       */
 int ga_set_launch_shape(ga_run *run, uint32_t block_threads,
                         uint32_t agents_per_thread);
@@ -610,16 +609,16 @@ int ga_set_launch_shape(ga_run *run, uint32_t block_threads,
 /* The resident form of a small synchronous run (on by default): when the
  * whole torus fits one workgroup's tile (at most 4,096 agents at the run's
  * agents per thread, on the fewest multiple of 64 threads that holds them,
- * within 64 KiB of LDS), each launch batch of ga_step is one launch of one
- * workgroup that takes the run through every generation of the batch,
- * with a workgroup barrier between generations instead of a kernel
- * boundary.  Results are the same as one launch per generation, which
+ * within 64 KiB of records), each launch batch of ga_step is one launch of
+ * one workgroup that takes the run through every generation of the batch
+ * in LDS, with a workgroup barrier between generations instead of a kernel
+ * boundary.  Results are the same as with launches over tiles, which
  * enable = 0 selects (the launch shape above then applies).  Asynchronous
  * runs and runs of a pool never step resident.  Errors: GA_EINVAL.         */
 int ga_set_resident(ga_run *run, int enable);
 
 /* *threads = the resident form's workgroup size for this run, or 0 when
- * the run steps one launch per generation.  Errors: GA_EINVAL.            */
+ * the run steps in launches over tiles.  Errors: GA_EINVAL.               */
 int ga_resident_threads(const ga_run *run, uint32_t *threads);
 
 #ifdef __cplusplus

@@ -423,9 +423,11 @@ namespace {
 
 // Workgroup size of the resident form for this run: the fewest multiple of
 // 64 threads that holds every agent at the run's agents per thread, so that
-// the whole torus is one tile; 0 when the run steps one launch per
-// generation instead (the form is off, the run is asynchronous or larger
-// than kResidentMaxAgents, or the tile would not fit the LDS).
+// the whole torus is one tile; 0 when the run steps in launches over tiles
+// instead (the form is off, the run is asynchronous or larger than
+// kResidentMaxAgents, or its records are over shape_lds_bytes' limit; many
+// small islands' entries and draws may take the launch over 64 KiB of LDS,
+// of the 160 KiB that a workgroup may have).
 uint32_t resident_block(const ga_run* r) {
     if (!r->resident || r->cfg.async_activity || r->A > kResidentMaxAgents) return 0;
     const uint32_t block = ((r->A + r->apt - 1) / r->apt + 63) / 64 * 64;

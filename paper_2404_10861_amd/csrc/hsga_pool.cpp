@@ -1,6 +1,6 @@
 // hsga_pool.cpp -- batched and served runs (include/hsga.h, ga_pool_*): a
 // first-fit allocator over the caller's arena, a device-resident run table,
-// and per generation one launch per group of active runs, the groups on
+// and per two generations one launch per group of active runs, the groups on
 // streams of their own that run side by side (optionally replayed from
 // captured hipGraphs).  The per-run arithmetic is step_tile and run_sites,
 // the same device code as the plain runs.
@@ -28,7 +28,7 @@ struct Slot {
 
 // An advance cuts the active runs, in table order, into kGroups
 // contiguous groups of about equal bytes per generation and gives each
-// group one launch per generation on a stream of its own.  The groups'
+// group one launch per two generations on a stream of its own.  The groups'
 // runs are independent, so the streams run side by side and one group's
 // launch tail (its last, partly filled wave of workgroups, and the gap
 // before its next launch) overlaps the others' work.  Only generations

@@ -106,3 +106,19 @@ def test_pool_of_ragged_tiles_matches_oracle(hs, orc):
             o = oracle_for(orc, c)
             o.step(20 + i)
             same_state(pool.run(k), o, f"run {i} at {block} threads")
+
+
+@pytest.mark.parametrize("W,H,N,S,kind,extra", [
+    # many small islands: more than 64 KiB of LDS for a resident workgroup
+    (32, 28, 4, 64, "hybrid", dict(tournament_size=2)),
+    (32, 32, 1, 64, "steady", FLOAT),
+    (32, 32, 2, 32, "tilted", dict(tournament_size=0)),
+])
+def test_resident_runs_of_many_small_islands_match_oracle(hs, orc, W, H, N, S, kind, extra):
+    c = hs.Config(W, H, N, S, kind, seed=12, **extra)
+    run, o = hs.Run(c), oracle_for(orc, c)
+    assert run.resident_threads > 0
+    for n in STEPS:
+        run.step(n)
+        o.step(n)
+        same_state(run, o, f"after a step of {n}")
