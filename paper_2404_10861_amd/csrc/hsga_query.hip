@@ -236,12 +236,10 @@ __device__ __forceinline__ uint64_t surface64(const uint32_t* __restrict__ surf,
 
 // Fast route: each annotation's differentiae in ascending-time order, packed
 // in 64 bits (rank r at bit r for one-bit differentiae, at byte r for bytes).
-__global__ __launch_bounds__(256) void mrca_rank_kernel(uint32_t S, uint32_t diff_log2,
-                                                       uint32_t n,
-                                                       const uint32_t* __restrict__ surf,
-                                                       const uint32_t* __restrict__ ws,
-                                                       uint64_t* __restrict__ ranked) {
-    if (ws[kWsStatus] != 0) return;
+__device__ __forceinline__ void rank_annotations(uint32_t S, uint32_t diff_log2, uint32_t n,
+                                                 const uint32_t* __restrict__ surf,
+                                                 const uint32_t* __restrict__ ws,
+                                                 uint64_t* __restrict__ ranked) {
     __shared__ uint32_t perm[64];
     if (threadIdx.x < 64) perm[threadIdx.x] = ws[kWsPerm + threadIdx.x];
     __syncthreads();
@@ -254,6 +252,15 @@ __global__ __launch_bounds__(256) void mrca_rank_kernel(uint32_t S, uint32_t dif
     for (uint32_t r = 0; r < F; ++r)
         packed |= ((s >> (perm[r] << diff_log2)) & mask) << (r << diff_log2);
     ranked[a] = packed;
+}
+
+__global__ __launch_bounds__(256) void mrca_rank_kernel(uint32_t S, uint32_t diff_log2,
+                                                       uint32_t n,
+                                                       const uint32_t* __restrict__ surf,
+                                                       const uint32_t* __restrict__ ws,
+                                                       uint64_t* __restrict__ ranked) {
+    if (ws[kWsStatus] != 0) return;
+    rank_annotations(S, diff_log2, n, surf, ws, ranked);
 }
 
 // Fast route, all ordered pairs: x = P_a xor P_b; the first set bit gives
@@ -324,15 +331,22 @@ __global__ __launch_bounds__(256) void mrca_allpairs_kernel(uint32_t n, uint32_t
 // General route (counters differ): one wavefront per annotation lays out
 // its own layout (from the rule's tables, else by replay) and stores its
 // retained deposit generations in ascending order with their sites.
-__global__ __launch_bounds__(64) void mrca_layouts_kernel(Scheme sc,
-                                                         const uint32_t* __restrict__ counter,
-                                                         const uint32_t* __restrict__ ws,
-                                                         uint32_t* __restrict__ times,
-                                                         uint8_t* __restrict__ sites,
-                                                         const RuleTable* __restrict__ rules) {
-    if (ws[kWsStatus] != kWsStatusMixed) return;
-    const uint32_t a = blockIdx.x;
-    const uint32_t lane = threadIdx.x;
+// One launch for either kind of query: annotations that share a counter are
+// put in time-rank order, one per thread of the first workgroups; those of
+// different ages are laid out, one per wavefront.
+__global__ __launch_bounds__(256) void mrca_annotations_kernel(
+    Scheme sc, uint32_t diff_log2, uint32_t n, const uint32_t* __restrict__ counter,
+    const uint32_t* __restrict__ surf, const uint32_t* __restrict__ ws,
+    uint64_t* __restrict__ ranked, uint32_t* __restrict__ times, uint8_t* __restrict__ sites,
+    const RuleTable* __restrict__ rules) {
+    const uint32_t status = ws[kWsStatus];
+    if (status == 0) {
+        if (blockIdx.x * blockDim.x < n) rank_annotations(sc.S, diff_log2, n, surf, ws, ranked);
+        return;
+    }
+    const uint32_t a = blockIdx.x * 4u + (threadIdx.x >> 6);
+    if (status != kWsStatusMixed || a >= n) return;
+    const uint32_t lane = threadIdx.x & 63u;
     const uint32_t S = sc.S;
     const uint32_t held = layout_lane(rules, sc.kind, S, ingests_of(counter[a], sc.interval), lane);
     const uint32_t rank = time_rank(held, lane, S);
@@ -989,12 +1003,10 @@ hipError_t launch_mrca(const Scheme& scm, uint32_t n, const uint32_t* counter,
 
     hipLaunchKernelGGL(mrca_prepare_kernel, dim3(1), dim3(kPrepareThreads), 0, stream, scm, n,
                        counter, ws, hint.layout, hint.T, hint.rules);
-    hipLaunchKernelGGL(mrca_rank_kernel, dim3((n + 255) / 256), dim3(256), 0, stream, S,
-                       diff_log2, n, surf, ws, ranked);
+    hipLaunchKernelGGL(mrca_annotations_kernel, dim3((n + 3) / 4), dim3(256), 0, stream, scm,
+                       diff_log2, n, counter, surf, ws, ranked, times, sites, hint.rules);
     hipLaunchKernelGGL(mrca_allpairs_kernel, dim3((n + 1023) / 1024, (n + kPairRows - 1) / kPairRows),
                        dim3(256), 0, stream, n, diff_log2, ranked, ws, lb, ub);
-    hipLaunchKernelGGL(mrca_layouts_kernel, dim3(n), dim3(64), 0, stream, scm, counter, ws,
-                       times, sites, hint.rules);
     constexpr uint32_t cols = kPairTileCols * kPairColTiles;
     hipLaunchKernelGGL(mrca_general_pairs_kernel,
                        dim3((n + cols - 1) / cols, (n + kPairTileRows - 1) / kPairTileRows),
