@@ -166,8 +166,8 @@ __device__ __forceinline__ double half_normal_radius(HalfNormalCoefficients K,
     const double q =
         __longlong_as_double((long long)((yb & kMantissa) | ((uint64_t)(1023 + (ex & 1)) << 52)));
     const double h = 0.5 * q;
-    double rs = __builtin_fma(
-        __builtin_fma(__builtin_fma(-0.01905041, q, 0.1946857), q, -0.73886303), q, 1.5561871);
+    double rs = series_step(
+        series_step(series_step(-0.01905041, q, 0.1946857), q, -0.73886303), q, 1.5561871);
 #pragma unroll
     for (int i = 0; i < 3; ++i) rs = __builtin_fma(rs, __builtin_fma(-h, rs * rs, 0.5), rs);
     double sq = q * rs;
