@@ -181,9 +181,13 @@ int run_init(ga_run* r, const ga_config* cfg, uint8_t* base, uint32_t gens, hipS
     r->apt = default_agents_per_thread(r->N);
     // 256 threads: a tile of 32 islands of 32 agents has 24 around it, and
     // their work and the islands' is a wavefront's or two of the tile's four
-    // (paper-scale run: 59.2 us per generation at 64 threads, 51.0 at 128,
-    // 47.8 at 256, 51.5 at 512; asynchronous ticks 82.3, 77.9, 72.3, 75.1)
-    r->block = 256u;
+    // (paper-scale run: 54.2 us per generation at 64 threads, 48.7 at 128,
+    // 45.8 at 256, 51.1 at 512; asynchronous ticks 79.9, 76.5, 71.6, 74.3).
+    // Up to half a million agents the chip is not full and more, smaller
+    // tiles spread them over more CUs (128 against 256 threads: 96 k agents
+    // 3.10 and 3.16 us, 320 k 3.54 and 3.71, float 7.23 and 7.35, ticks 4.64
+    // and 5.01; 640 k 4.41 and 4.22)
+    r->block = r->A <= (1u << 19) ? 128u : 256u;
     r->timing = false;
     hipError_t e = hsga::launch_founders(r->trait[0], r->counter[0], r->surf[0], r->A, r->SW,
                                          r->layout, r->S, cfg->fitness_model == GA_FOUNDER_TAG,
