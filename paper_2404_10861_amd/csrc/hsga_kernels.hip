@@ -581,7 +581,7 @@ __device__ __forceinline__ void step_births(const StepParams& p, const uint32_t*
 // front, sine cases from the back) and evaluated after all births in rounds
 // of the wave's lanes, so the draw runs once per mutating birth rather than
 // once per birth for the whole wave, and no round mixes the two series.
-template <int SW, int APT, bool ASYNC, bool POW2>
+template <int SW, int APT, bool ASYNC, bool POW2, bool WHOLE>
 __device__ __forceinline__ void step_float_births(const StepParams& p, const uint32_t* lds,
                                                   uint32_t TA, uint32_t base, uint32_t j0,
                                                   uint32_t isl, uint32_t g, const Deposit& dep,
@@ -592,7 +592,7 @@ __device__ __forceinline__ void step_float_births(const StepParams& p, const uin
     const uint32_t* l_trait = lds;
     uint32_t fslot = 0, ncos = 0, nsin = 0;
     bool mutates[APT], worse[APT];
-    const uint2 key = run_key<true>(p);
+    const uint2 key = run_key<!WHOLE>(p);
 #pragma unroll
     for (int q0 = 0; q0 < APT; q0 += K) {
         BirthDraws<kBirthFloat, K> draws;
@@ -638,12 +638,15 @@ __device__ __forceinline__ void step_float_births(const StepParams& p, const uin
     // LDS writes land before its later reads), then each birth's fitness
     const uint64_t ex = __ballot(true);
     const uint32_t me = lanes_below(ex), na = (uint32_t)__popcll(ex);
+    // (a resident run, which waits for each load, loads the coefficients
+    // once a generation)
+    const HalfNormalCoefficients kept = half_normal_coefficients();
     auto evaluate = [&](uint32_t n, bool sine) __attribute__((always_inline)) {
         for (uint32_t b0 = 0; b0 < n; b0 += na) {
             if (b0 + me < n) {
                 const uint32_t i = sine ? QC - 1u - (b0 + me) : b0 + me;
                 const uint2 e = wq[i];
-                const HalfNormalCoefficients K = half_normal_coefficients();
+                const HalfNormalCoefficients K = WHOLE ? kept : half_normal_coefficients();
                 double z = half_normal_radius(K, e.x);
                 if (sine) z *= half_normal_angle<true>(K, e.y);
                 else z *= half_normal_angle<false>(K, e.y);
@@ -972,10 +975,10 @@ __device__ __forceinline__ void step_tile(const StepParams& p, uint32_t tile) {
                 if constexpr (BM == kBirthFloat) {
                     uint2* wq = reinterpret_cast<uint2*>(lds + L.queue) + (t >> 6) * (64u * APT);
                     if (n_shift)
-                        step_float_births<SW, APT, ASYNC, true>(p, lds, TA, base, j0, isl, g, dep,
+                        step_float_births<SW, APT, ASYNC, true, WHOLE>(p, lds, TA, base, j0, isl, g, dep,
                                                                 n_shift, wq, kid);
                     else
-                        step_float_births<SW, APT, ASYNC, false>(p, lds, TA, base, j0, isl, g, dep,
+                        step_float_births<SW, APT, ASYNC, false, WHOLE>(p, lds, TA, base, j0, isl, g, dep,
                                                                  n_shift, wq, kid);
                 } else if (n_shift) {
                     step_births<SW, BM, APT, ASYNC, true>(p, lds, TA, base, draws, dep, n_shift,
