@@ -446,7 +446,9 @@ __global__ __launch_bounds__(kPairTileCols) void mrca_general_pairs_kernel(
         if (b0 >= n) break;
         const uint32_t b = b0 + tid;
         const uint64_t sb = b < n ? surface64(surf, SW, b) : 0ull;
-        // (a column past n is later than every row: it takes no part)
+        // (a column past n takes no part: it is not stored directly, and no
+        // row is above its counter in the transposed stores; a row may be
+        // equal to it, since 2^32 - 1 is a counter too)
         const uint32_t Tb = b < n ? counter[b] : kEmpty;
         __syncthreads();          // tables built; the last tile's stage read
         T_col[tid] = Tb;
@@ -469,7 +471,7 @@ __global__ __launch_bounds__(kPairTileCols) void mrca_general_pairs_kernel(
                 }
                 u4[q] = r < kNoRank ? t_of[row][r] : kEmpty;
                 l4[q] = r - 1u < kNoRank - 1u ? t_of[row][r - 1u] + 1u : 0u;
-                const bool later = Tb <= T_row[row];
+                const bool later = b < n && Tb <= T_row[row];
                 if (later && u4[q] >= Tb) {
                     // no mismatch: the last of a's items older than Tb
                     uint32_t f = 0;
