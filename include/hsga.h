@@ -599,9 +599,10 @@ int ga_probe_copy(const void *src, void *dst, size_t bytes, void *hip_stream);
  * 4 gives 16-byte population loads and stores).  A workgroup handles a
  * tile of at most block_threads * agents_per_thread / N whole islands
  * (256 at most), staged in LDS (at most 64 KiB), for two generations per
- * launch; the library chooses the tile's sides.  0 keeps the current
- * value.  Results do not depend on the shape.  A run starts at 4 agents
- * per thread when N allows, with 256 threads (128 up to 2^19 agents).
+ * launch, or one where births are float; the library chooses the tile's
+ * sides.  0 keeps the current value.  Results do not depend on the shape.
+ * A run starts at 4 agents per thread when N allows, with 256 threads (128
+ * up to 2^19 agents, but for float births on islands below 32 agents).
  * Errors: GA_EINVAL.                                                       */
 int ga_set_launch_shape(ga_run *run, uint32_t block_threads,
                         uint32_t agents_per_thread);

@@ -470,7 +470,7 @@ class Run(RunHandle):
 
     def set_resident(self, enable: bool = True):
         """The resident form for a run that fits one workgroup (default on);
-        False: one launch per generation at the launch shape."""
+        False: launches over tiles at the launch shape."""
         _check(load_library().ga_set_resident(self._h, 1 if enable else 0))
 
     @property

@@ -185,9 +185,11 @@ int run_init(ga_run* r, const ga_config* cfg, uint8_t* base, uint32_t gens, hipS
     // 45.8 at 256, 51.1 at 512; asynchronous ticks 79.9, 76.5, 71.6, 74.3).
     // Up to half a million agents the chip is not full and more, smaller
     // tiles spread them over more CUs (128 against 256 threads: 96 k agents
-    // 3.10 and 3.16 us, 320 k 3.54 and 3.71, float 7.23 and 7.35, ticks 4.64
-    // and 5.01; 640 k 4.41 and 4.22)
-    r->block = r->A <= (1u << 19) ? 128u : 256u;
+    // 3.10 and 3.16 us, 320 k 3.54 and 3.71, ticks 4.64 and 5.01, float 5.9
+    // and 6.1; 640 k 4.41 and 4.22; but float runs of 16 agents to an island
+    // 6.6 and 6.1)
+    const bool float_births = birth_model(*cfg) == hsga::kBirthFloat;
+    r->block = r->A <= (1u << 19) && (!float_births || r->N >= 32) ? 128u : 256u;
     r->timing = false;
     hipError_t e = hsga::launch_founders(r->trait[0], r->counter[0], r->surf[0], r->A, r->SW,
                                          r->layout, r->S, cfg->fitness_model == GA_FOUNDER_TAG,
@@ -228,7 +230,7 @@ hsga::TileGeom make_tile(const ga_run* r, uint32_t w, uint32_t h, bool whole) {
     t.w = (uint16_t)w;
     t.h = (uint16_t)h;
     t.cols = (uint16_t)((r->cfg.grid_w + w - 1) / w);
-    t.rows = (uint16_t)((r->cfg.grid_h + h - 1) / h);
+    t.tiles = t.cols * ((r->cfg.grid_h + h - 1) / h);
     t.threads = (uint16_t)((w * h * (r->N / r->apt) + 63) / 64 * 64);
     t.whole = whole ? 1 : 0;
     t.n_magic = ((1u << 20) + r->N - 1) / r->N;
@@ -242,6 +244,22 @@ hsga::TileGeom make_tile(const ga_run* r, uint32_t w, uint32_t h, bool whole) {
     t.draws = (uint8_t)(whole ? std::min(std::max(t.threads / (2 * w * h), 1u), 8u)
                               : hsga::kTileGens);
     hsga::column_magic(whole ? w * h : t.cols, &t.cols_magic, &shift);
+    t.cols_shift = (uint16_t)shift;
+    return t;
+}
+
+// A tile of `islands` consecutive islands.
+hsga::TileGeom make_line(const ga_run* r, uint32_t islands, uint32_t threads) {
+    hsga::TileGeom t{};
+    t.w = (uint16_t)islands;
+    t.h = 1;
+    t.threads = (uint16_t)threads;
+    t.line = 1;
+    t.draws = 1;
+    t.tiles = (r->I + islands - 1) / islands;
+    t.n_magic = ((1u << 20) + r->N - 1) / r->N;
+    uint32_t shift;
+    hsga::column_magic(r->cfg.grid_w, &t.cols_magic, &shift);
     t.cols_shift = (uint16_t)shift;
     return t;
 }
@@ -261,6 +279,12 @@ size_t tile_lds(const ga_run* r, const hsga::TileGeom& t) {
 // whose rows are the longest contiguous pieces.
 const hsga::TileGeom& run_tile(ga_run* r, uint32_t block) {
     if (r->tile_block == block && r->tile_apt == r->apt) return r->tile;
+    r->tile_block = block;
+    r->tile_apt = r->apt;
+    if (hsga::line_tiles(birth_model(r->cfg), r->cfg.migrants_per_island != 0)) {
+        r->tile = make_line(r, std::min(tile_islands(block, r->apt, r->N), block), block);
+        return r->tile;
+    }
     const uint32_t W = r->cfg.grid_w, H = r->cfg.grid_h;
     const uint32_t most = std::min(tile_islands(block, r->apt, r->N), kMaxTileIslands);
     uint64_t best = ~0ull;
@@ -274,14 +298,12 @@ const hsga::TileGeom& run_tile(ga_run* r, uint32_t block) {
             t = make_tile(r, --w, h, false);
         if (2 * (w + h) > t.threads || tile_lds(r, t) > kMaxStepLds) break;
         const uint64_t lanes = t.threads * r->apt + (uint64_t)(w + h) * r->N / 2;
-        const uint64_t cost = lanes * t.cols * t.rows;
+        const uint64_t cost = lanes * t.tiles;
         if (cost < best) {
             best = cost;
             r->tile = t;
         }
     }
-    r->tile_block = block;
-    r->tile_apt = r->apt;
     return r->tile;
 }
 
@@ -468,7 +490,7 @@ int step_enqueue(ga_run* r, uint32_t n) {
     // without migration an island needs nothing of the others, so a tile's
     // launch takes as many generations as a batch has
     const uint32_t per = cfg.migrants_per_island == 0 && cfg.async_activity == 0
-                             ? r->gens : hsga::kTileGens;
+                             ? r->gens : run_tile(r, r->block).draws;
     if (cfg.async_activity) {
         // asynchronous ticks: each birth finds its site from its parent's
         // counter in the rule's tables

@@ -127,6 +127,18 @@ __device__ __forceinline__ HalfNormalCoefficients half_normal_coefficients() {
     return K;
 }
 
+// The radius's coefficients in scalar registers, all loaded at once.
+struct RadiusRegisters {
+    double r[11];
+    __device__ __forceinline__ void load(HalfNormalCoefficients K) {
+#pragma unroll
+        for (int k = 0; k < 11; ++k) r[k] = K[k];
+        asm volatile("" : "+s"(r[0]), "+s"(r[1]), "+s"(r[2]), "+s"(r[3]), "+s"(r[4]), "+s"(r[5]),
+                          "+s"(r[6]), "+s"(r[7]), "+s"(r[8]), "+s"(r[9]), "+s"(r[10]));
+    }
+    __device__ __forceinline__ double operator[](int k) const { return r[k]; }
+};
+
 // sqrt(-2 ln U1).  1/sqrt q starts from a cubic instead of the
 // definition's 9/8 - 3q/16 and so takes three Newton steps where it takes
 // six: 12 instructions for 19, with the same result to the last bit for each
@@ -134,8 +146,8 @@ __device__ __forceinline__ HalfNormalCoefficients half_normal_coefficients() {
 // correction step squares what is left of the error, a rounding in either
 // case).  1/(m+1) keeps the definition's five steps from 1/2: they stop
 // 1e-22 off at the ends, which the last rounding does see for a few words.
-__device__ __forceinline__ double half_normal_radius(HalfNormalCoefficients K,
-                                                     uint32_t w_radius) {
+template <class Coefficients>
+__device__ __forceinline__ double half_normal_radius(const Coefficients& K, uint32_t w_radius) {
 #pragma clang fp contract(off)
     // ln U1.  v = 2 w_radius + 1 < 2^33 is exact in binary64; its exponent
     // is floor(log2 v), and setting the exponent to 0 gives v 2^-e exactly
@@ -180,8 +192,8 @@ __device__ __forceinline__ double half_normal_radius(HalfNormalCoefficients K,
 // (2 w_angle + 1) in the sine case, is an exact binary64 integer; the 2^-33
 // is folded into pi/2 (an exact power-of-two scaling of it, so the product
 // rounds the same).
-template <bool SIN>
-__device__ __forceinline__ double half_normal_angle(HalfNormalCoefficients K, uint32_t w_angle) {
+template <bool SIN, class Coefficients>
+__device__ __forceinline__ double half_normal_angle(const Coefficients& K, uint32_t w_angle) {
 #pragma clang fp contract(off)
     const double wad = (double)w_angle;
     const double va = SIN ? __builtin_fma(-2.0, wad, 8589934591.0) : __builtin_fma(2.0, wad, 1.0);
@@ -192,14 +204,6 @@ __device__ __forceinline__ double half_normal_angle(HalfNormalCoefficients K, ui
 #pragma unroll
     for (int k = first + 1; k < first + 10; ++k) c = series_step(c, x2, K[k]);
     return SIN ? x * c : c;
-}
-
-// The draw.
-__device__ __forceinline__ double half_normal(uint32_t w_radius, uint32_t w_angle) {
-    const HalfNormalCoefficients K = half_normal_coefficients();
-    const double radius = half_normal_radius(K, w_radius);
-    return radius * (w_angle >= 0x80000000u ? half_normal_angle<true>(K, w_angle)
-                                            : half_normal_angle<false>(K, w_angle));
 }
 
 // The fitness after a draw: f - del_sigma |Z| (deleterious) or

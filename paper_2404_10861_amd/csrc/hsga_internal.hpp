@@ -30,20 +30,29 @@ enum BirthModel : uint32_t {
 // emigrants of the islands around a tile reach one generation ahead.
 constexpr uint32_t kTileGens = 2;
 
-// A workgroup's tile of whole islands: w x h islands of the torus in
-// cols x rows tiles (the last ones of a row or column may be ragged), or
-// the whole torus (whole).
+// Float births with migration step over line tiles, one generation per
+// launch.
+constexpr bool line_tiles(uint32_t birth_model, bool migration) {
+    return birth_model == kBirthFloat && migration;
+}
+
+// A workgroup's tile of whole islands: w x h islands of the torus, cols
+// tiles to a row of them (the last ones of a row or column may be ragged);
+// the whole torus (whole); or w islands in a row of the population (line).
 struct TileGeom {
-    uint16_t w, h, cols, rows;
+    uint16_t w, h, cols;
     uint16_t threads;                  // of its workgroup
-    uint8_t whole;
-    uint8_t draws;                     // generations whose island draws are held at once
+    uint8_t whole, line;
+    uint8_t draws;                     // generations whose island draws are held at once (of
+                                       // tiles: a launch's generations)
     uint16_t pw_shift, cols_shift;
+    uint32_t tiles;                    // of the run
     uint32_t n_magic;                  // ceil(2^20 / N): la / N == (la * n_magic) >> 20, la < 4096
     uint32_t w_magic;                  // the same for w, below 1,024 islands
     uint32_t isl_magic;                // the same for w h <= 256, below 2,048
     uint32_t pw_magic;                 // e / (w + 2) by multiplication (column_magic)
-    uint32_t cols_magic;               // tile / cols (the whole torus: draw / its islands)
+    uint32_t cols_magic;               // tile / cols (the whole torus: draw / its islands;
+                                       // a line: island / the torus's side)
 };
 
 struct StepParams {
@@ -79,8 +88,8 @@ struct StepParams {
 };
 
 // One run of a batched launch: a device-resident table entry, written by the
-// host before each batch.  Launch k steps generations T0 + k kTileGens on,
-// from buffers k & 1 into the others; a run that has done its gens sits the
+// host before each batch.  Launch k steps the tile's generations (tile.draws)
+// from T0 + k tile.draws on, from buffers k & 1 into the others; a run that has done its gens sits the
 // launch out.
 struct BatchRun {
     uint32_t* trait[2];        // [0]: the run's current population
@@ -152,8 +161,8 @@ hipError_t launch_fill_site_ring(const RuleTable* rules, uint32_t kind, uint32_t
 hipError_t launch_set_layout(uint32_t* layout, const uint32_t* words, uint32_t S,
                              hipStream_t stream);
 
-// Generations p.g .. p.g + p.gens - 1 (at most kTileGens with migration or
-// asynchronous ticks, any number in a tile that is the whole torus: the
+// Generations p.g .. p.g + p.gens - 1 (one over line tiles, otherwise at most
+// kTileGens with migration or asynchronous ticks, any number in a tile that is the whole torus: the
 // resident form, one workgroup, synchronous runs only).  agents_per_thread
 // (1, 2 or 4) must divide N; the tile's agents fit its threads.
 hipError_t launch_step(const StepParams& p, uint32_t SW, uint32_t birth_model, bool migration,
@@ -163,7 +172,7 @@ hipError_t launch_step(const StepParams& p, uint32_t SW, uint32_t birth_model, b
 // after them (launch_run_sites per run); max_gens bounds every run's gens.
 hipError_t launch_batch_sites(const BatchRun* runs, uint32_t nruns, uint32_t max_gens,
                               hipStream_t stream);
-// Launch k, kTileGens generations of every run: total_tiles workgroups, workgroup b on XCD
+// Launch k, the next generations (tile.draws) of every run: total_tiles workgroups, workgroup b on XCD
 // b mod kXcds as its (b / kXcds)-th.  xcd_tab (2 * kXcds * nruns words):
 // for each XCD x, pre[x][i] = the offset of run i's chunk among x's
 // workgroups (ascending in i, pre[x][0] = 0); then for each XCD x,

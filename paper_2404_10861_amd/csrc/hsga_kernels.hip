@@ -9,6 +9,8 @@
 // island * N + slot.  Consecutive
 // lanes own consecutive agents, so every population read and write is a
 // contiguous 256-byte wavefront access per plane.
+#include <type_traits>
+
 #include "hsga_device.hpp"
 #include "hsga_internal.hpp"
 #include "hsga_layout.hpp"
@@ -342,10 +344,16 @@ __device__ __forceinline__ uint32_t deposited(uint32_t word, int w, const Deposi
 
 // ... of generation g of a synchronous run, whose parents all carry
 // counter g: the batch's schedule.
-__device__ __forceinline__ Deposit scheduled_deposit(const StepParams& p, uint32_t g) {
+template <class Word>
+__device__ __forceinline__ Deposit scheduled_deposit(const StepParams& p, uint32_t g,
+                                                     Word* sites) {
     const uint32_t tau = p.interval == 1u ? g : g / p.interval;
     if (tau * p.interval != g) return {{0u, 0u}, 0u};
-    return deposit_at(p.sites[tau - p.tau0], p.diff_log2);
+    return deposit_at(sites[tau - p.tau0], p.diff_log2);
+}
+
+__device__ __forceinline__ Deposit scheduled_deposit(const StepParams& p, uint32_t g) {
+    return scheduled_deposit(p, g, p.sites);
 }
 
 __device__ __forceinline__ uint32_t int_mutation(const StepParams& p, uint32_t test,
@@ -380,25 +388,21 @@ __device__ __forceinline__ void post_entry(uint32_t* o, const Emigrant& e) {
 }
 
 // The emigrant that an island around a tile posts in generation p.g, its
-// slot and direction drawn already: that slot's birth, from P_g and O_g in
-// memory.  A drawn candidate is an immigrant where the last arrival written
-// to its slot says so.  load() issues everything the birth may need at once
-// (a float birth's surface, of up to five candidates, is left until its
-// parent is known), so that the few lanes that work one out wait once, and
+// slot and direction drawn already: that slot's (integer) birth, from P_g
+// and O_g in memory.  A drawn candidate is an immigrant where the last
+// arrival written to its slot says so.  load() issues everything the birth
+// may need at once, so that the few lanes that work one out wait once, and
 // that behind the loads of the tile and the birth draws; child() is the
 // birth.
 template <int SW, uint32_t BM, bool ASYNC>
 struct RingBirth {
     static constexpr uint32_t OBW = ASYNC ? kOutboxWords : kSyncOutboxWords;
-    static constexpr bool FLOAT = BM == kBirthFloat;
-    static constexpr int NC = FLOAT ? 5 : (BM == kBirthIntTournament ? 2 : 1);
+    static constexpr int NC = BM == kBirthIntTournament ? 2 : 1;
     uint4 en[4];                          // the neighbours' entries (SW > 1 ticks: and hi)
     uint32_t hi[4];
     uint32_t tr[NC], cn[NC], sf[NC][SW];  // the candidates' records
-    uint32_t slots;                       // 6 bits per candidate
     uint32_t match;                       // bit 4c + d: direction d's immigrant has c's slot
-    uint32_t w0, w1, w2;                  // int: r.z, r.w; float: v.y, v.z, v.w
-    size_t a0;                            // the island's first agent
+    uint32_t w0, w1;                      // the birth's words r.z, r.w
 
     __device__ __forceinline__ void load(const StepParams& p, uint32_t isl, uint32_t x,
                                          uint32_t slot) {
@@ -409,38 +413,28 @@ struct RingBirth {
             en[d] = *reinterpret_cast<const uint4*>(o);
             if (ASYNC && SW > 1) hi[d] = o[4];
         }
-        uint4 b[FLOAT ? 3 : 2];
-        b[0] = make_uint4(slot, isl, p.g, kBirth);
-        b[1] = make_uint4(0u, isl, p.g, kImmigrate);
-        if constexpr (FLOAT) b[2] = make_uint4(slot, isl, p.g, kBirthB);
+        uint4 b[2] = {make_uint4(slot, isl, p.g, kBirth), make_uint4(0u, isl, p.g, kImmigrate)};
         const uint2 key = run_key<true>(p);
-        philox4x32_10_multi<FLOAT ? 3 : 2>(b, key.x, key.y);
-        const uint4 r = b[0];
-        const uint4 v = b[FLOAT ? 2 : 0];
-        const uint32_t words[5] = {r.x, r.y, r.z, r.w, v.x};
+        philox4x32_10_multi<2>(b, key.x, key.y);
+        const uint32_t words[2] = {b[0].x, b[0].y};
         const uint32_t imm[4] = {word_below(b[1].x, N), word_below(b[1].y, N),
                                  word_below(b[1].z, N), word_below(b[1].w, N)};
-        a0 = (size_t)isl * N;
-        slots = 0;
+        const size_t a0 = (size_t)isl * N;
         match = 0;
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
             const uint32_t cand = word_below(words[c], N);
             tr[c] = p.in_trait[a0 + cand];
-            if constexpr (!FLOAT) {
-                if constexpr (ASYNC) cn[c] = p.in_counter[a0 + cand];
+            if constexpr (ASYNC) cn[c] = p.in_counter[a0 + cand];
 #pragma unroll
-                for (int w = 0; w < SW; ++w) sf[c][w] = p.in_surf[(size_t)w * p.A + a0 + cand];
-            }
-            slots |= cand << (6 * c);
+            for (int w = 0; w < SW; ++w) sf[c][w] = p.in_surf[(size_t)w * p.A + a0 + cand];
 #pragma unroll
             for (uint32_t d = 0; d < 4; ++d) match |= (imm[d] == cand ? 1u : 0u) << (4 * c + d);
         }
         // before the first generation no entry was posted
         if (!p.has_inbox) match = 0;
-        w0 = FLOAT ? v.y : r.z;
-        w1 = FLOAT ? v.z : r.w;
-        w2 = FLOAT ? v.w : r.w;
+        w0 = b[0].z;
+        w1 = b[0].w;
     }
 
     __device__ __forceinline__ Emigrant child(const StepParams& p, uint32_t dir, Deposit dep) {
@@ -448,7 +442,7 @@ struct RingBirth {
         uint32_t sent = 0;
 #pragma unroll
         for (uint32_t d = 0; d < 4; ++d) sent |= (en[d].x == (d ^ 1u) ? 1u : 0u) << d;
-        uint32_t best = 0, src = 0, par = 0, T = p.g, s[SW] = {};
+        uint32_t best = 0, src = 0, T = p.g, s[SW] = {};
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
             // the directions whose immigrant candidate c is; the last one wins
@@ -459,31 +453,18 @@ struct RingBirth {
                 const uint32_t y = en[d].y;
                 t = (arr >> d) & 1u ? y : t;
             }
-            bool win = c == 0;
-            if constexpr (FLOAT)
-                win = win || ((uint32_t)c < p.tour && __uint_as_float(t) > __uint_as_float(best));
-            else
-                win = win || (int32_t)t > (int32_t)best;
+            const bool win = c == 0 || (int32_t)t > (int32_t)best;
             best = win ? t : best;
             src = win ? arr : src;
-            if constexpr (FLOAT) {
-                par = win ? (slots >> (6 * c)) & 63u : par;
-            } else {
-                if constexpr (ASYNC) {
-                    const uint32_t n = cn[c];
-                    T = win ? n : T;
-                }
-#pragma unroll
-                for (int w = 0; w < SW; ++w) {
-                    const uint32_t f = sf[c][w], o = s[w];
-                    s[w] = win ? f : o;
-                }
+            if constexpr (ASYNC) {
+                const uint32_t n = cn[c];
+                T = win ? n : T;
             }
-        }
-        if constexpr (FLOAT) {
-            if constexpr (ASYNC) T = p.in_counter[a0 + par];
 #pragma unroll
-            for (int w = 0; w < SW; ++w) s[w] = p.in_surf[(size_t)w * p.A + a0 + par];
+            for (int w = 0; w < SW; ++w) {
+                const uint32_t f = sf[c][w], o = s[w];
+                s[w] = win ? f : o;
+            }
         }
 #pragma unroll
         for (uint32_t d = 0; d < 4; ++d) {
@@ -495,18 +476,10 @@ struct RingBirth {
             s[0] = it ? e0 : f0;
             if (SW > 1) s[SW - 1] = it ? e1 : f1;
         }
-        if constexpr (FLOAT) {
-            if (float_mutates(p, w0)) {
-                const double z = half_normal(w1, w2);
-                best = __float_as_uint(apply_half_normal(
-                    __uint_as_float(best), w0 < p.del_thr ? p.del_scale : p.ben_scale, z));
-            }
-        } else {
-            best += int_mutation(p, w0, w1);
-        }
+        best += int_mutation(p, w0, w1);
         if constexpr (ASYNC) dep = deposit_of(p, T);
-        return {dir, best, T + 1u, deposited(s[0], 0, dep, w2),
-                SW > 1 ? deposited(s[SW - 1], 1, dep, w2) : 0u};
+        return {dir, best, T + 1u, deposited(s[0], 0, dep, w1),
+                SW > 1 ? deposited(s[SW - 1], 1, dep, w1) : 0u};
     }
 };
 
@@ -527,6 +500,41 @@ __device__ __forceinline__ void keep_agents(const uint32_t* lds, uint32_t TA, ui
         for (int w = 0; w < SW; ++w) kid.sf[w].v[q] = lds[(1 + w) * TA + la0 + q];
         kid.cn.v[q] = lds[(1 + SW) * TA + la0 + q];
     }
+}
+
+// The island's emigrant (its emigration word), if it is one of the thread's
+// agents (slots j0 on), to the entry o.
+template <int SW, int APT, bool ASYNC>
+__device__ __forceinline__ void post_emigrant(uint32_t* o, uint32_t emig, uint32_t j0,
+                                              const Children<SW, APT>& kid) {
+    const uint32_t qe = (emig & 0xffu) - j0;            // >= APT: another thread's
+    if (qe >= (uint32_t)APT) return;
+    Emigrant out{emig >> 8, kid.tr.v[0], ASYNC ? kid.cn.v[0] : 0u, kid.sf[0].v[0],
+                 SW > 1 ? kid.sf[SW - 1].v[0] : 0u};
+#pragma unroll
+    for (int q = 1; q < APT; ++q) {
+        const bool it = qe == (uint32_t)q;
+        const uint32_t a = kid.tr.v[q], b = kid.sf[0].v[q], c = kid.sf[SW - 1].v[q];
+        out.trait = it ? a : out.trait;
+        if constexpr (ASYNC) {
+            const uint32_t d = kid.cn.v[q];
+            out.counter = it ? d : out.counter;
+        }
+        out.s0 = it ? b : out.s0;
+        if (SW > 1) out.s1 = it ? c : out.s1;
+    }
+    post_entry<ASYNC>(o, out);
+}
+
+// The children into the planes, from agent ga on.
+template <int SW, int APT, bool ASYNC>
+__device__ __forceinline__ void store_children(const StepParams& p, uint32_t ga,
+                                               const Children<SW, APT>& kid) {
+    store_lanes<APT>(p.out_trait, ga, kid.tr);
+    // a synchronous run keeps no counter plane: every counter is the generation
+    if constexpr (ASYNC) store_lanes<APT>(p.out_counter, ga, kid.cn);
+#pragma unroll
+    for (int w = 0; w < SW; ++w) store_lanes<APT>(p.out_surf + (size_t)w * p.A, ga, kid.sf[w]);
 }
 
 // The rest of a birth once its parent (LDS agent par) is chosen: its
@@ -581,29 +589,45 @@ __device__ __forceinline__ void step_births(const StepParams& p, const uint32_t*
 // front, sine cases from the back) and evaluated after all births in rounds
 // of the wave's lanes, so the draw runs once per mutating birth rather than
 // once per birth for the whole wave, and no round mixes the two series.
-template <int SW, int APT, bool ASYNC, bool POW2, bool WHOLE>
+template <int SW, int APT, bool ASYNC, bool POW2, bool WHOLE, bool DRAWN = false>
 __device__ __forceinline__ void step_float_births(const StepParams& p, const uint32_t* lds,
                                                   uint32_t TA, uint32_t base, uint32_t j0,
                                                   uint32_t isl, uint32_t g, const Deposit& dep,
                                                   uint32_t n_shift, uint2* wq,
-                                                  Children<SW, APT>& kid) {
-    constexpr int K = APT < 2 ? APT : 2;
+                                                  Children<SW, APT>& kid,
+                                                  const BirthDraws<kBirthFloat, APT>* drawn) {
+    constexpr int K = DRAWN ? APT : (APT < 2 ? APT : 2);
     constexpr uint32_t QC = 64u * APT;
     const uint32_t* l_trait = lds;
     uint32_t fslot = 0, ncos = 0, nsin = 0;
     bool mutates[APT], worse[APT];
+    auto enqueue = [&](int q, const uint4& v) __attribute__((always_inline)) {
+        mutates[q] = float_mutates(p, v.y);
+        worse[q] = v.y < p.del_thr;
+        const bool sn = v.w >= 0x80000000u;              // the draw's sine case
+        const uint64_t mc = __ballot(mutates[q] && !sn);
+        const uint64_t ms = __ballot(mutates[q] && sn);
+        if (mutates[q]) {
+            const uint32_t slot = sn ? QC - 1u - lanes_below(ms, nsin) : lanes_below(mc, ncos);
+            wq[slot] = make_uint2(v.z, v.w);
+            fslot |= slot << (8 * q);
+        }
+        ncos += (uint32_t)__popcll(mc);
+        nsin += (uint32_t)__popcll(ms);
+    };
     const uint2 key = run_key<!WHOLE>(p);
 #pragma unroll
     for (int q0 = 0; q0 < APT; q0 += K) {
         BirthDraws<kBirthFloat, K> draws;
-        draws.compute(key, j0 + q0, isl, g);
+        if constexpr (!DRAWN) draws.compute(key, j0 + q0, isl, g);
 #pragma unroll
         for (int i = 0; i < K; ++i) {
             // tournament of p.tour draws (words r.x, r.y, r.z, r.w, v.x),
             // the first of maximal fitness winning; mutation class from
             // v.y, |Z| from v.z and v.w, differentia the low bits of v.w
             const int q = q0 + i;
-            const uint4 r = draws.blk[i], v = draws.blk[K + i];
+            const uint4 r = DRAWN ? drawn->blk[q] : draws.blk[i];
+            const uint4 v = DRAWN ? drawn->blk[APT + q] : draws.blk[K + i];
             uint32_t par = base + pick_slot<POW2>(r.x, p.N, n_shift);
             float best = __uint_as_float(l_trait[par]);
             const uint32_t words[4] = {r.y, r.z, r.w, v.x};
@@ -620,43 +644,47 @@ __device__ __forceinline__ void step_float_births(const StepParams& p, const uin
             }
             kid.tr.v[q] = __float_as_uint(best);         // the draw is applied below
             inherit<SW, APT, ASYNC>(p, lds, TA, par, v.w, dep, q, kid);
-            mutates[q] = float_mutates(p, v.y);
-            worse[q] = v.y < p.del_thr;
-            const bool sn = v.w >= 0x80000000u;          // the draw's sine case
-            const uint64_t mc = __ballot(mutates[q] && !sn);
-            const uint64_t ms = __ballot(mutates[q] && sn);
-            if (mutates[q]) {
-                const uint32_t slot = sn ? QC - 1u - lanes_below(ms, nsin) : lanes_below(mc, ncos);
-                wq[slot] = make_uint2(v.z, v.w);
-                fslot |= slot << (8 * q);
-            }
-            ncos += (uint32_t)__popcll(mc);
-            nsin += (uint32_t)__popcll(ms);
+            if constexpr (!DRAWN) enqueue(q, v);
         }
+    }
+    // (all four births' reads before the queue's first write, which would
+    // hold up those after it)
+    if constexpr (DRAWN) {
+#pragma unroll
+        for (int q = 0; q < APT; ++q) enqueue(q, drawn->blk[APT + q]);
     }
     // the queued draws in rounds of the active lanes (one wavefront: its
     // LDS writes land before its later reads), then each birth's fitness
     const uint64_t ex = __ballot(true);
     const uint32_t me = lanes_below(ex), na = (uint32_t)__popcll(ex);
-    // (a resident run, which waits for each load, loads the coefficients
-    // once a generation)
+    // (a resident run loads the coefficients once a generation, a draw of a
+    // synchronous line tile the radius's all at once: taken as the steps come
+    // to them they would be waited for four times instead of twice.  Ticks,
+    // short of scalar registers, take them so)
+    constexpr bool HELD = DRAWN && !ASYNC;
     const HalfNormalCoefficients kept = half_normal_coefficients();
-    auto evaluate = [&](uint32_t n, bool sine) __attribute__((always_inline)) {
+    auto evaluate = [&](uint32_t n, auto sine) __attribute__((always_inline)) {
+        constexpr bool SIN = decltype(sine)::value;
         for (uint32_t b0 = 0; b0 < n; b0 += na) {
             if (b0 + me < n) {
-                const uint32_t i = sine ? QC - 1u - (b0 + me) : b0 + me;
+                const uint32_t i = SIN ? QC - 1u - (b0 + me) : b0 + me;
                 const uint2 e = wq[i];
                 const HalfNormalCoefficients K = WHOLE ? kept : half_normal_coefficients();
-                double z = half_normal_radius(K, e.x);
-                if (sine) z *= half_normal_angle<true>(K, e.y);
-                else z *= half_normal_angle<false>(K, e.y);
+                double z;
+                if constexpr (HELD) {
+                    RadiusRegisters radius;
+                    radius.load(K);
+                    z = half_normal_radius(radius, e.x);
+                }
+                else z = half_normal_radius(K, e.x);
+                z *= half_normal_angle<SIN>(K, e.y);
                 const uint64_t zb = (uint64_t)__double_as_longlong(z);
                 wq[i] = make_uint2((uint32_t)zb, (uint32_t)(zb >> 32));
             }
         }
     };
-    evaluate(ncos, false);
-    evaluate(nsin, true);
+    evaluate(ncos, std::false_type{});
+    evaluate(nsin, std::true_type{});
 #pragma unroll
     for (int q = 0; q < APT; ++q) {
         if (mutates[q]) {
@@ -976,10 +1004,10 @@ __device__ __forceinline__ void step_tile(const StepParams& p, uint32_t tile) {
                     uint2* wq = reinterpret_cast<uint2*>(lds + L.queue) + (t >> 6) * (64u * APT);
                     if (n_shift)
                         step_float_births<SW, APT, ASYNC, true, WHOLE>(p, lds, TA, base, j0, isl, g, dep,
-                                                                n_shift, wq, kid);
+                                                                n_shift, wq, kid, nullptr);
                     else
                         step_float_births<SW, APT, ASYNC, false, WHOLE>(p, lds, TA, base, j0, isl, g, dep,
-                                                                 n_shift, wq, kid);
+                                                                 n_shift, wq, kid, nullptr);
                 } else if (n_shift) {
                     step_births<SW, BM, APT, ASYNC, true>(p, lds, TA, base, draws, dep, n_shift,
                                                           kid);
@@ -994,32 +1022,15 @@ __device__ __forceinline__ void step_tile(const StepParams& p, uint32_t tile) {
             }
         }
     };
-    // the island's emigrant, if it is one of this thread's agents
-    auto post = [&](uint32_t* o) __attribute__((always_inline)) {
-        const uint32_t qe = (emig & 0xffu) - j0;        // >= APT: another thread's
-        if (!mine || qe >= (uint32_t)APT) return;
-        Emigrant out{emig >> 8, kid.tr.v[0], ASYNC ? kid.cn.v[0] : 0u, kid.sf[0].v[0],
-                     SW > 1 ? kid.sf[SW - 1].v[0] : 0u};
-#pragma unroll
-        for (int q = 1; q < APT; ++q) {
-            const bool it = qe == (uint32_t)q;
-            const uint32_t a = kid.tr.v[q], b = kid.sf[0].v[q], c = kid.sf[SW - 1].v[q];
-            out.trait = it ? a : out.trait;
-            if constexpr (ASYNC) {
-                const uint32_t d = kid.cn.v[q];
-                out.counter = it ? d : out.counter;
-            }
-            out.s0 = it ? b : out.s0;
-            if (SW > 1) out.s1 = it ? c : out.s1;
-        }
-        post_entry<ASYNC>(o, out);
-    };
     // the children of generation k are the next one's parents (every parent
     // has been read), and the next generation's draws and deposit
     auto succeed = [&](uint32_t k) __attribute__((always_inline)) {
         if (own) wave_order();
         else __syncthreads();
-        if constexpr (MIGR) post(lds + L.entries + (((k & 1u) ? 0u : L.NE) + eidx) * OBW);
+        if constexpr (MIGR)
+            if (mine)
+                post_emigrant<SW, APT, ASYNC>(lds + L.entries + (((k & 1u) ? 0u : L.NE) + eidx) * OBW,
+                                              emig, j0, kid);
         if (mine) {
             lds_store_lanes<APT>(l_trait + la0, kid.tr);
             if constexpr (ASYNC) lds_store_lanes<APT>(l_count + la0, kid.cn);
@@ -1055,23 +1066,205 @@ __device__ __forceinline__ void step_tile(const StepParams& p, uint32_t tile) {
             advance(1u);
         }
     }
-    if constexpr (MIGR) post(p.ob_out + (size_t)isl * OBW);
     if (mine) {
-        store_lanes<APT>(p.out_trait, ga, kid.tr);
-        // a synchronous run keeps no counter plane: every counter is g + gens
-        if constexpr (ASYNC) store_lanes<APT>(p.out_counter, ga, kid.cn);
-#pragma unroll
-        for (int w = 0; w < SW; ++w) store_lanes<APT>(p.out_surf + w * A, ga, kid.sf[w]);
+        if constexpr (MIGR)
+            post_emigrant<SW, APT, ASYNC>(p.ob_out + (size_t)isl * OBW, emig, j0, kid);
+        store_children<SW, APT, ASYNC>(p, ga, kid);
     }
 }
 
-// Float births are bound by VALU issue (98 % of it): registers for seven
-// wavefronts per SIMD instead of six are worth the few scalar spills that
-// they cost (float trial 112.0 -> 109.7 us per generation).
+// The LDS of a line tile, in words: trait, surface and (asynchronous ticks)
+// counter planes of TA words, an emigration word per island, then the draw
+// queues.
+struct LineLds {
+    uint32_t TA, emig, queue;
+};
+
+__host__ __device__ inline LineLds line_lds(uint32_t islands, uint32_t N, uint32_t SW,
+                                            bool async) {
+    LineLds l;
+    l.TA = (islands * N + 3u) & ~3u;
+    l.emig = (1u + SW + (async ? 1u : 0u)) * l.TA;
+    l.queue = (l.emig + islands + 3u) & ~3u;
+    return l;
+}
+
+// A line tile: one generation, with migration, of p.tile.w islands in a row
+// of the population (they may run over several of the torus).  An island's
+// four entries go from memory to the lane that draws its slots, which writes
+// the immigrants after the staging.
+//
+// The form of float births, whose launch is bound by VALU issue: the planes'
+// second trip through memory hides behind the births, while a second
+// generation's emigrants from around the tile, few lanes of a wave with a
+// half-normal each, make 958 VALU instructions per wavefront and generation
+// of 828 (18 M agents, tournament of five: 112.4 us per generation in
+// launches of two, 105.2 here; one-word surfaces 107.3 and 97.2; ticks of
+// 8.4 M agents 71.6 and 68.4).  A run below half a million agents is bound
+// by its chain of latencies instead: the arguments' cache lines are asked for
+// at once, the coefficients' while the planes are on their way, and the
+// schedule's word by a scalar load (96 k agents 6.28 us in launches of two,
+// 5.88 here; 6.2 without those three).
+template <int SW, uint32_t BM, int APT, bool ASYNC>
+__device__ __forceinline__ void step_line(const StepParams& p, uint32_t tile) {
+    constexpr uint32_t OBW = ASYNC ? kOutboxWords : kSyncOutboxWords;
+    uint32_t* lds = g_step_lds;
+    const uint32_t N = p.N, W = p.W;
+    const LineLds L = line_lds(p.tile.w, N, SW, ASYNC);
+    const uint32_t TA = L.TA;
+    uint32_t* l_trait = lds;
+    uint32_t* l_surf = lds + TA;                       // SW planes of TA words
+    uint32_t* l_count = lds + (1 + SW) * TA;           // asynchronous ticks only
+    uint32_t* l_emig = lds + L.emig;
+    const size_t A = p.A;
+    const uint32_t t = threadIdx.x;
+    const uint32_t la0 = t * APT;
+    const uint32_t first = tile * p.tile.w;            // the tile's islands
+    const uint32_t nisl = min((uint32_t)p.tile.w, p.I - first);
+    const bool mine = la0 < nisl * N;
+    const uint32_t ga = first * N + la0;
+
+    // 1. the loads, all issued before anything waits for one (as in step_tile)
+    __builtin_amdgcn_s_setprio(3);
+    Lanes<APT> tr, ct, sf[SW];
+    if (mine) {
+        tr = load_lanes<APT>(p.in_trait, ga);
+        if (ASYNC) ct = load_lanes<APT>(p.in_counter, ga);
+#pragma unroll
+        for (int w = 0; w < SW; ++w) sf[w] = load_lanes<APT>(p.in_surf + w * A, ga);
+    }
+    // thread t takes island t's immigrants; lanes without one read entry 0,
+    // outside any branch (before the first generation the entries are read
+    // but not used).  Only wavefronts that hold an island work out indices.
+    size_t e[4] = {0, 0, 0, 0};
+    if ((uint32_t)__builtin_amdgcn_readfirstlane((int)t) < nisl) {
+        const bool lane_isl = t < nisl;
+        const uint32_t isl = first + (lane_isl ? t : 0u);
+        const uint32_t x = isl - quotient_of(isl, p.tile.cols_magic, p.tile.cols_shift) * W;
+#pragma unroll
+        for (uint32_t d = 0; d < 4; ++d)
+            e[d] = lane_isl ? (size_t)neighbour_of(isl, x, d, W, p.I) * OBW : 0;
+    }
+    uint4 in_lo[4];
+    uint32_t in_hi[4];
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        in_lo[d] = *reinterpret_cast<const uint4*>(p.ob_in + e[d]);
+        if (ASYNC && SW > 1) in_hi[d] = p.ob_in[e[d] + 4];
+    }
+    __builtin_amdgcn_s_setprio(0);
+    // the islands' draws, one lane each: immigration by the lane that holds
+    // the island's entries, emigration by the lanes after (or, where the
+    // islands take more than half of them, by the same ones)
+    uint32_t imm_slots = 0;
+    bool imm_take = false;
+    const uint2 key = run_key<true>(p);
+    auto active = [&](uint32_t isl) {
+        // asynchronous ticks: an idle island takes no immigrants and posts
+        // no emigrant
+        if constexpr (ASYNC)
+            return philox4x32_10(make_uint4(0u, isl, p.g, kActivity), key.x, key.y).x <
+                   p.async_thr;
+        return true;
+    };
+    // the half-normal's coefficients, a word of each of their cache lines,
+    // while the planes are on their way: the births load them when they need them
+    if constexpr (BM == kBirthFloat) {
+        const HalfNormalCoefficients K = half_normal_coefficients();
+        asm volatile("" ::"s"(K[0]), "s"(K[8]), "s"(K[16]), "s"(K[24]), "s"(K[30]));
+    }
+    auto draw_island = [&](uint32_t il, bool imm) {
+        const uint32_t isl = first + il;
+        const bool act = active(isl);
+        const uint4 w4 = philox4x32_10(make_uint4(0u, isl, p.g, imm ? kImmigrate : kEmigrate),
+                                       key.x, key.y);
+        if (!imm) {
+            l_emig[il] = word_below(w4.x, N) | ((act ? w4.y >> 30 : 4u) << 8);
+        } else if (p.has_inbox && act) {
+            imm_slots = word_below(w4.x, N) | (word_below(w4.y, N) << 6) |
+                        (word_below(w4.z, N) << 12) | (word_below(w4.w, N) << 18);
+            imm_take = true;
+        }
+    };
+    // (the schedule is of an earlier launch, so a scalar load: a vector load
+    // here would be waited for with the planes)
+    typedef const __attribute__((address_space(4))) uint32_t Scheduled;
+    Deposit dep{{0u, 0u}, 0u};
+    if constexpr (!ASYNC) dep = scheduled_deposit(p, p.g, (Scheduled*)p.sites);
+    if (2u * nisl <= blockDim.x) {
+        if (t < 2u * nisl) draw_island(t < nisl ? t : t - nisl, t < nisl);
+    } else if (t < nisl) {
+        draw_island(t, true);
+        draw_island(t, false);
+    }
+    // this thread's island and first slot (one division: la0 < 4096), and its
+    // birth draws while the loads are in flight (a float birth's two blocks
+    // an agent would cost a wave per SIMD here)
+    const uint32_t lil = (la0 * p.tile.n_magic) >> 20;
+    const uint32_t j0 = la0 - lil * N, isl = first + lil;
+    BirthDraws<BM, APT> draws;
+    if constexpr (BM != kBirthFloat)
+        if (mine) draws.compute(key, j0, isl, p.g);
+    // 2. stage the tile, then the immigrants over the drawn slots (north,
+    // south, west, east: a later direction overwrites an earlier one)
+    if (mine) {
+        lds_store_lanes<APT>(l_trait + la0, tr);
+        if (ASYNC) lds_store_lanes<APT>(l_count + la0, ct);
+#pragma unroll
+        for (int w = 0; w < SW; ++w) lds_store_lanes<APT>(l_surf + w * TA + la0, sf[w]);
+    }
+    __syncthreads();
+    if (imm_take) {
+#pragma unroll
+        for (uint32_t d = 0; d < 4; ++d) {
+            // a neighbour delivers when its emigrant was sent our way
+            if (in_lo[d].x == (d ^ 1u)) {
+                const uint32_t la = t * N + ((imm_slots >> (6u * d)) & 63u);
+                l_trait[la] = in_lo[d].y;
+                if constexpr (ASYNC) l_count[la] = in_lo[d].z;
+                l_surf[la] = ASYNC ? in_lo[d].w : in_lo[d].z;
+                if (SW > 1) l_surf[TA + la] = ASYNC ? in_hi[d] : in_lo[d].w;
+            }
+        }
+    }
+    __syncthreads();
+    // 3. births
+    if (!mine) return;
+    const uint32_t emig = l_emig[lil], base = lil * N;
+    Children<SW, APT> kid;
+    if (ASYNC && (emig >> 8) == 4u) {
+        keep_agents<SW, APT>(lds, TA, la0, kid);
+    } else {
+        if constexpr (BM == kBirthFloat) draws.compute(key, j0, isl, p.g);
+        const uint32_t n_shift = (N > 1u && (N & (N - 1u)) == 0u) ? 32u - __builtin_ctz(N) : 0u;
+        // a wave-uniform choice between two copies of the births
+        if constexpr (BM == kBirthFloat) {
+            uint2* wq = reinterpret_cast<uint2*>(lds + L.queue) + (t >> 6) * (64u * APT);
+            if (n_shift)
+                step_float_births<SW, APT, ASYNC, true, false, true>(
+                    p, lds, TA, base, j0, isl, p.g, dep, n_shift, wq, kid, &draws);
+            else
+                step_float_births<SW, APT, ASYNC, false, false, true>(
+                    p, lds, TA, base, j0, isl, p.g, dep, n_shift, wq, kid, &draws);
+        } else if (n_shift) {
+            step_births<SW, BM, APT, ASYNC, true>(p, lds, TA, base, draws, dep, n_shift, kid);
+        } else {
+            step_births<SW, BM, APT, ASYNC, false>(p, lds, TA, base, draws, dep, n_shift, kid);
+        }
+    }
+    post_emigrant<SW, APT, ASYNC>(p.ob_out + (size_t)isl * OBW, emig, j0, kid);
+    store_children<SW, APT, ASYNC>(p, ga, kid);
+}
+
+template <int SW, uint32_t BM, int APT, bool ASYNC>
+__global__ __launch_bounds__(1024) void line_kernel(const StepParams p) {
+    // a word of each cache line of the arguments, all on their way at once
+    asm volatile("" ::"s"(p.in_trait), "s"(p.sites), "s"(p.tile.n_magic), "s"(p.interval));
+    step_line<SW, BM, APT, ASYNC>(p, xcd_local_block(blockIdx.x, gridDim.x));
+}
+
 template <int SW, uint32_t BM, bool MIGR, int APT, bool ASYNC>
-__global__ __launch_bounds__(1024)
-__attribute__((amdgpu_waves_per_eu(BM == kBirthFloat && !ASYNC ? 7 : 1, 8)))
-void step_kernel(const StepParams p) {
+__global__ __launch_bounds__(1024) void step_kernel(const StepParams p) {
     step_tile<SW, BM, MIGR, APT, ASYNC, false>(p, xcd_local_block(blockIdx.x, gridDim.x));
 }
 
@@ -1086,6 +1279,9 @@ __global__ __launch_bounds__(1024) void resident_step_kernel(const StepParams p)
 
 size_t step_lds_bytes(const TileGeom& tg, uint32_t N, uint32_t SW, bool async,
                       bool float_births, uint32_t apt) {
+    if (tg.line)
+        return 4 * (size_t)line_lds(tg.w, N, SW, async).queue +
+               (float_births ? 8 * (size_t)tg.threads * apt : 0);
     const bool whole = tg.whole != 0;
     const uint32_t RI = tg.w * tg.h;
     const TileLds l = tile_lds(RI, whole ? RI : (tg.w + 2u) * (tg.h + 2u), N, SW, async,
@@ -1107,11 +1303,15 @@ static hipError_t launch_step_t(const StepParams& p, hipStream_t stream) {
             hipLaunchKernelGGL((resident_step_kernel<SW, BM, MIGR, APT>), dim3(1),
                                dim3(tg.threads), lds, stream, p);
         }
+    } else if constexpr (line_tiles(BM, MIGR)) {
+        if (!tg.line || p.gens != 1 || tg.w > tg.threads) return hipErrorInvalidValue;
+        hipLaunchKernelGGL((line_kernel<SW, BM, APT, ASYNC>), dim3(tg.tiles), dim3(tg.threads),
+                           lds, stream, p);
     } else {
         // more generations than the emigrants around a tile reach
         if (p.gens > kTileGens && (MIGR || ASYNC)) return hipErrorInvalidValue;
         if (2u * (tg.w + tg.h) > tg.threads) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((step_kernel<SW, BM, MIGR, APT, ASYNC>), dim3(tg.cols * tg.rows),
+        hipLaunchKernelGGL((step_kernel<SW, BM, MIGR, APT, ASYNC>), dim3(tg.tiles),
                            dim3(tg.threads), lds, stream, p);
     }
     return hipGetLastError();
@@ -1157,8 +1357,9 @@ hipError_t launch_step(const StepParams& p, uint32_t SW, uint32_t birth_model, b
 
 // ---------------------------------------------------------------------------
 // Batched forms: many runs of different sizes, surfaces, treatments and
-// agents per thread in one launch per generation, sharing step_tile and
-// run_sites with the plain forms.
+// agents per thread in one launch, each run stepping its own tiles'
+// generations of it, sharing step_tile, step_line and run_sites with the
+// plain forms.
 __global__ __launch_bounds__(256) void batch_sites_kernel(const BatchRun* __restrict__ runs) {
     const BatchRun& R = runs[blockIdx.y];
     const uint32_t tau0 = ingests_of(R.T0, R.interval);
@@ -1175,11 +1376,17 @@ hipError_t launch_batch_sites(const BatchRun* runs, uint32_t nruns, uint32_t max
     return hipGetLastError();
 }
 
+template <int SW, uint32_t BM, bool MIGR, int APT>
+__device__ __forceinline__ void step_batched(const StepParams& p, uint32_t tile) {
+    if constexpr (line_tiles(BM, MIGR)) step_line<SW, BM, APT, false>(p, tile);
+    else step_tile<SW, BM, MIGR, APT, false, false>(p, tile);
+}
+
 template <int SW, uint32_t BM, bool MIGR>
 __device__ __forceinline__ void step_tile_apt(const StepParams& p, uint32_t tile, uint32_t apt_log2) {
-    if (apt_log2 == 2) step_tile<SW, BM, MIGR, 4, false, false>(p, tile);
-    else if (apt_log2 == 1) step_tile<SW, BM, MIGR, 2, false, false>(p, tile);
-    else step_tile<SW, BM, MIGR, 1, false, false>(p, tile);
+    if (apt_log2 == 2) step_batched<SW, BM, MIGR, 4>(p, tile);
+    else if (apt_log2 == 1) step_batched<SW, BM, MIGR, 2>(p, tile);
+    else step_batched<SW, BM, MIGR, 1>(p, tile);
 }
 
 template <uint32_t BM>
@@ -1227,8 +1434,11 @@ __global__ __launch_bounds__(1024) void batch_step_kernel(const BatchRun* __rest
     const uint32_t lo = before - 1u;       // pre[0] = 0: at least one run
     const BatchRun& R = runs[lo];
     const uint32_t t = xcd_tab[(kXcds + x) * nruns + lo] + (j - pre[lo]);
-    if (k * kTileGens >= R.gens) return;
-    const uint32_t g = R.T0 + k * kTileGens;
+    // (a constant where no run steps otherwise: read from the table it would
+    // be one more wait before the tile's loads, 2 % of 64 batched runs)
+    const uint32_t per = WITH_FLOAT ? R.tile.draws : kTileGens;
+    if (k * per >= R.gens) return;
+    const uint32_t g = R.T0 + k * per;
     const uint32_t src = k & 1u, dst = src ^ 1u;
     StepParams p;
     p.in_trait = R.trait[src];
@@ -1246,7 +1456,7 @@ __global__ __launch_bounds__(1024) void batch_step_kernel(const BatchRun* __rest
     p.I = R.W * R.H;
     p.A = p.I * R.N;
     p.g = g;
-    p.gens = min(kTileGens, R.gens - k * kTileGens);
+    p.gens = min(per, R.gens - k * per);
     p.k0 = R.k0; p.k1 = R.k1;
     p.mut_thr = R.mut_thr; p.mut_lo = R.mut_lo; p.mut_span = R.mut_span;
     const bool mig = (R.variant >> 3) & 1u;

@@ -1,6 +1,7 @@
 // hsga_pool.cpp -- batched and served runs (include/hsga.h, ga_pool_*): a
 // first-fit allocator over the caller's arena, a device-resident run table,
-// and per two generations one launch per group of active runs, the groups on
+// and per two generations (one while float runs with migration are among them)
+// one launch per group of active runs, the groups on
 // streams of their own that run side by side (optionally replayed from
 // captured hipGraphs).  The per-run arithmetic is step_tile and run_sites,
 // the same device code as the plain runs.
@@ -28,7 +29,7 @@ struct Slot {
 
 // An advance cuts the active runs, in table order, into kGroups
 // contiguous groups of about equal bytes per generation and gives each
-// group one launch per two generations on a stream of its own.  The groups'
+// group one launch per two generations (or one) on a stream of its own.  The groups'
 // runs are independent, so the streams run side by side and one group's
 // launch tail (its last, partly filled wave of workgroups, and the gap
 // before its next launch) overlaps the others' work.  Only generations
@@ -157,8 +158,8 @@ void release_handles(ga_pool* p) {
 // surface words, in and out (the balance of the launch groups)
 uint64_t words_per_generation(const ga_run& r) { return (uint64_t)r.A * (1 + r.SW); }
 
-// launches that take a run through g generations
-uint32_t launches_of(uint32_t g) { return (g + hsga::kTileGens - 1) / hsga::kTileGens; }
+// launches that take a run through g generations over its tiles
+uint32_t launches_of(uint32_t g, const hsga::TileGeom& t) { return (g + t.draws - 1) / t.draws; }
 
 uint32_t variant_of(const ga_run& r) {
     uint32_t v = 0;
@@ -433,12 +434,12 @@ int ga_pool_advance(ga_pool* p, uint32_t max_gens, uint32_t* gens_enqueued) {
         b.interval = r.cfg.ingest_interval;
         b.diff_log2 = sp.diff_log2;
         b.tile = tile;
-        const uint32_t rt = tile.cols * tile.rows;
+        const uint32_t rt = tile.tiles;
         run_tiles[i] = rt;
         grp.tiles += rt;
         ++grp.count;
         key.gens = std::max(key.gens, g);
-        key.launches = std::max(key.launches, launches_of(g));
+        key.launches = std::max(key.launches, launches_of(g, tile));
         grp.lds = std::max(grp.lds, hsga::step_lds_bytes(tile, r.N, r.SW, false,
                                                          birth_model(r.cfg) == hsga::kBirthFloat,
                                                          r.apt));
@@ -475,7 +476,7 @@ int ga_pool_advance(ga_pool* p, uint32_t max_gens, uint32_t* gens_enqueued) {
     for (uint32_t i = 0; i < nruns; ++i) {
         Slot& s = p->slots[active[i]];
         s.run.T += p->h_table[i].gens;
-        s.run.cur ^= launches_of(p->h_table[i].gens) & 1u;
+        s.run.cur ^= launches_of(p->h_table[i].gens, p->h_table[i].tile) & 1u;
     }
     if (gens_enqueued) *gens_enqueued = key.gens;
     return GA_OK;
