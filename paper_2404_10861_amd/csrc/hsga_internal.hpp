@@ -40,19 +40,19 @@ constexpr bool line_tiles(uint32_t birth_model, bool migration) {
 // tiles to a row of them (the last ones of a row or column may be ragged);
 // the whole torus (whole); or w islands in a row of the population (line).
 struct TileGeom {
-    uint16_t w, h, cols;
+    uint16_t w, h, cols, line;
     uint16_t threads;                  // of its workgroup
-    uint8_t whole, line;
+    uint8_t whole;
     uint8_t draws;                     // generations whose island draws are held at once (of
                                        // tiles: a launch's generations)
     uint16_t pw_shift, cols_shift;
-    uint32_t tiles;                    // of the run
     uint32_t n_magic;                  // ceil(2^20 / N): la / N == (la * n_magic) >> 20, la < 4096
     uint32_t w_magic;                  // the same for w, below 1,024 islands
     uint32_t isl_magic;                // the same for w h <= 256, below 2,048
     uint32_t pw_magic;                 // e / (w + 2) by multiplication (column_magic)
     uint32_t cols_magic;               // tile / cols (the whole torus: draw / its islands;
                                        // a line: island / the torus's side)
+    uint32_t tiles;                    // of the run
 };
 
 struct StepParams {

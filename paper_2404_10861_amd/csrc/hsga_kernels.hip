@@ -503,12 +503,13 @@ __device__ __forceinline__ void keep_agents(const uint32_t* lds, uint32_t TA, ui
 }
 
 // The island's emigrant (its emigration word), if it is one of the thread's
-// agents (slots j0 on), to the entry o.
+// agents (slots j0 on; mine: it has any), to the entry o.  (The test of mine
+// stands here: a branch around the call has cost small resident runs 5 %.)
 template <int SW, int APT, bool ASYNC>
-__device__ __forceinline__ void post_emigrant(uint32_t* o, uint32_t emig, uint32_t j0,
+__device__ __forceinline__ void post_emigrant(uint32_t* o, bool mine, uint32_t emig, uint32_t j0,
                                               const Children<SW, APT>& kid) {
     const uint32_t qe = (emig & 0xffu) - j0;            // >= APT: another thread's
-    if (qe >= (uint32_t)APT) return;
+    if (!mine || qe >= (uint32_t)APT) return;
     Emigrant out{emig >> 8, kid.tr.v[0], ASYNC ? kid.cn.v[0] : 0u, kid.sf[0].v[0],
                  SW > 1 ? kid.sf[SW - 1].v[0] : 0u};
 #pragma unroll
@@ -1028,9 +1029,8 @@ __device__ __forceinline__ void step_tile(const StepParams& p, uint32_t tile) {
         if (own) wave_order();
         else __syncthreads();
         if constexpr (MIGR)
-            if (mine)
-                post_emigrant<SW, APT, ASYNC>(lds + L.entries + (((k & 1u) ? 0u : L.NE) + eidx) * OBW,
-                                              emig, j0, kid);
+            post_emigrant<SW, APT, ASYNC>(lds + L.entries + (((k & 1u) ? 0u : L.NE) + eidx) * OBW,
+                                          mine, emig, j0, kid);
         if (mine) {
             lds_store_lanes<APT>(l_trait + la0, kid.tr);
             if constexpr (ASYNC) lds_store_lanes<APT>(l_count + la0, kid.cn);
@@ -1066,11 +1066,9 @@ __device__ __forceinline__ void step_tile(const StepParams& p, uint32_t tile) {
             advance(1u);
         }
     }
-    if (mine) {
-        if constexpr (MIGR)
-            post_emigrant<SW, APT, ASYNC>(p.ob_out + (size_t)isl * OBW, emig, j0, kid);
-        store_children<SW, APT, ASYNC>(p, ga, kid);
-    }
+    if constexpr (MIGR)
+        post_emigrant<SW, APT, ASYNC>(p.ob_out + (size_t)isl * OBW, mine, emig, j0, kid);
+    if (mine) store_children<SW, APT, ASYNC>(p, ga, kid);
 }
 
 // The LDS of a line tile, in words: trait, surface and (asynchronous ticks)
@@ -1252,7 +1250,7 @@ __device__ __forceinline__ void step_line(const StepParams& p, uint32_t tile) {
             step_births<SW, BM, APT, ASYNC, false>(p, lds, TA, base, draws, dep, n_shift, kid);
         }
     }
-    post_emigrant<SW, APT, ASYNC>(p.ob_out + (size_t)isl * OBW, emig, j0, kid);
+    post_emigrant<SW, APT, ASYNC>(p.ob_out + (size_t)isl * OBW, true, emig, j0, kid);
     store_children<SW, APT, ASYNC>(p, ga, kid);
 }
 
