@@ -598,11 +598,14 @@ int ga_probe_copy(const void *src, void *dst, size_t bytes, void *hip_stream);
  * 64..1024) and agents per thread (1, 2 or 4; must divide pop_per_island;
  * 4 gives 16-byte population loads and stores).  A workgroup handles a
  * tile of at most block_threads * agents_per_thread / N whole islands
- * (256 at most), staged in LDS (at most 64 KiB), for two generations per
- * launch, or one where births are float; the library chooses the tile's
- * sides.  0 keeps the current value.  Results do not depend on the shape.
- * A run starts at 4 agents per thread when N allows, with 256 threads (128
- * up to 2^19 agents, but for float births on islands below 32 agents).
+ * (on at most 256 threads, outside a pool), staged in LDS (at most 64 KiB),
+ * for two generations per launch, or one where births are float or the
+ * islands around a tile are many for its agents; the library chooses the
+ * tile's sides.  0 keeps the current value.  Results do not depend on the
+ * shape.  A run starts at 4 agents per thread when N allows, with 128
+ * threads up to 114,688 agents, or 2^19 on islands of 16 agents and more
+ * (32 for float births) at 4 per thread, otherwise 256; islands of 4 start
+ * at 64 or 128.
  * Errors: GA_EINVAL.                                                       */
 int ga_set_launch_shape(ga_run *run, uint32_t block_threads,
                         uint32_t agents_per_thread);

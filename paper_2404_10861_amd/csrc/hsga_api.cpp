@@ -147,6 +147,38 @@ namespace {
 uint32_t default_agents_per_thread(uint32_t N) {
     return N % 4 == 0 ? 4u : (N % 2 == 0 ? 2u : 1u);
 }
+
+// Whether a run steps over line tiles, one generation per launch, or over
+// tiles of two.  Float births with migration always do.  Integer births do
+// where the islands around a tile are many for the agents in it: few agents
+// to an island, or one agent per thread (an odd number to an island), where
+// a launch is bound by VALU issue as soon as the chip is full.  The lines are
+// drawn where the two forms were equal on runs of 2^16 to 2^23 agents in steps
+// of sqrt 2 (us per generation, two generations and line: N = 1, 2^19 agents
+// 8.8 and 7.1, 2^23 86 and 82; N = 3, 2^21 17.5 and 15.2, 2^17.5 3.6 and 4.1;
+// N = 4, 2^20 8.4 and 7.4, 2^22.5 26 and 27.5; N = 17, 2^22 28.0 and 22.8, 2^20
+// 8.7 and 8.7, 2^18 3.8 and 5.2).  Ticks on two-word surfaces are bound by
+// memory and keep two where an island has an odd number above one.  A pool's
+// integer runs always keep two: both forms' code in the batched kernel made 64
+// runs 7 % slower.
+bool line_pays(const ga_run* r, uint32_t block) {
+    const ga_config& cfg = r->cfg;
+    if (cfg.migrants_per_island == 0) return false;
+    if (hsga::line_only(birth_model(cfg), true)) return true;
+    if (r->pooled) return false;
+    const bool ticks = cfg.async_activity != 0, wide = r->SW == 2;
+    const uint32_t A = r->A, N = r->N;
+    if (r->apt == 4) return N == 4 && (ticks ? wide || A < 1u << 22 : A < 5u << 19);
+    if (r->apt == 2) {
+        if (N == 2) return ticks ? A < 3u << 18 : !wide || A < 3u << 20;
+        return block == 64 && !ticks && !wide && A > 3u << 18;
+    }
+    if (ticks && wide) return N == 1 && A < 3u << 17;
+    if (N == 1) return !ticks || A < 7u << 17;
+    if (N <= 3 || (ticks && N <= 5)) return A > 1u << 18;
+    return A > (block < 256 ? 3u << 18 : wide ? 15u << 17 : 3u << 19);
+}
+
 }  // namespace
 
 int run_init(ga_run* r, const ga_config* cfg, uint8_t* base, uint32_t gens, hipStream_t stream) {
@@ -186,10 +218,16 @@ int run_init(ga_run* r, const ga_config* cfg, uint8_t* base, uint32_t gens, hipS
     // Up to half a million agents the chip is not full and more, smaller
     // tiles spread them over more CUs (128 against 256 threads: 96 k agents
     // 3.10 and 3.16 us, 320 k 3.54 and 3.71, ticks 4.64 and 5.01, float 5.9
-    // and 6.1; 640 k 4.41 and 4.22; but float runs of 16 agents to an island
-    // 6.6 and 6.1)
+    // and 6.1; 640 k 4.41 and 4.22), or up to 114,688 where a thread holds
+    // fewer than four or an island few (runs of 17 agents to an island: 65 k
+    // 2.80 and 2.95, 512 k 5.9 and 5.6; float runs of 16: 160 k 6.6 and 6.1)
     const bool float_births = birth_model(*cfg) == hsga::kBirthFloat;
-    r->block = r->A <= (1u << 19) && (!float_births || r->N >= 32) ? 128u : 256u;
+    r->block = r->A < (7u << 14) || (r->A <= (1u << 19) && r->apt == 4 &&
+                                     r->N >= (float_births ? 32u : 16u)) ? 128u : 256u;
+    // islands of four agents over line tiles: 64 threads on two-word surfaces
+    // and 128 on one-word ones (2^21 agents 12.7 and 14.6 us at 64 and 256)
+    if (r->apt == 4 && line_pays(r, r->block) && !float_births)
+        r->block = r->SW == 2 && !cfg->async_activity ? 64u : 128u;
     r->timing = false;
     hipError_t e = hsga::launch_founders(r->trait[0], r->counter[0], r->surf[0], r->A, r->SW,
                                          r->layout, r->S, cfg->fitness_model == GA_FOUNDER_TAG,
@@ -271,6 +309,10 @@ size_t tile_lds(const ga_run* r, const hsga::TileGeom& t) {
 
 }  // namespace
 
+hsga::TileGeom line_tile(const ga_run* r, uint32_t block) {
+    return make_line(r, std::min(tile_islands(block, r->apt, r->N), block), block);
+}
+
 // The tile with the least work for the whole torus: every workgroup takes
 // the time of its wavefronts, full or not, and about a quarter of a birth
 // island's for each island around the tile (only those whose emigrant comes
@@ -281,8 +323,9 @@ const hsga::TileGeom& run_tile(ga_run* r, uint32_t block) {
     if (r->tile_block == block && r->tile_apt == r->apt) return r->tile;
     r->tile_block = block;
     r->tile_apt = r->apt;
-    if (hsga::line_tiles(birth_model(r->cfg), r->cfg.migrants_per_island != 0)) {
-        r->tile = make_line(r, std::min(tile_islands(block, r->apt, r->N), block), block);
+    if (!r->pooled) block = std::min(block, kMaxTileThreads);
+    if (line_pays(r, block)) {
+        r->tile = line_tile(r, block);
         return r->tile;
     }
     const uint32_t W = r->cfg.grid_w, H = r->cfg.grid_h;
@@ -473,7 +516,12 @@ int enqueue_steps(ga_run* r, const hsga::TileGeom& tile, uint32_t done, uint32_t
     const bool mig = r->cfg.migrants_per_island != 0;
     for (uint32_t k = 0; k < n; k += per) {
         const uint32_t gens = std::min(per, n - k);
-        const hsga::StepParams p = step_params(r, r->T + done + k, gens, r->cur, tau0, tile);
+        // a launch of a single generation has nothing to gain from the islands
+        // around its tiles (16.8 M agents 75 us over tiles of two, 71 over a line;
+        // 96 k agents 4.7 and 3.9)
+        const bool single = mig && gens == 1 && !tile.whole && !tile.line;
+        const hsga::StepParams p = step_params(r, r->T + done + k, gens, r->cur, tau0,
+                                               single ? line_tile(r, std::min(r->block, kMaxTileThreads)) : tile);
         hipError_t e = hsga::launch_step(p, r->SW, model, mig, r->apt, r->stream);
         if (e != hipSuccess) return hip_fail(e, "step launch");
         r->cur ^= 1u;

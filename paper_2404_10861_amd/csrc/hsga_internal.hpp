@@ -30,9 +30,9 @@ enum BirthModel : uint32_t {
 // emigrants of the islands around a tile reach one generation ahead.
 constexpr uint32_t kTileGens = 2;
 
-// Float births with migration step over line tiles, one generation per
-// launch.
-constexpr bool line_tiles(uint32_t birth_model, bool migration) {
+// Float births with migration always step over line tiles, one generation
+// per launch.
+constexpr bool line_only(uint32_t birth_model, bool migration) {
     return birth_model == kBirthFloat && migration;
 }
 

@@ -1301,10 +1301,16 @@ static hipError_t launch_step_t(const StepParams& p, hipStream_t stream) {
             hipLaunchKernelGGL((resident_step_kernel<SW, BM, MIGR, APT>), dim3(1),
                                dim3(tg.threads), lds, stream, p);
         }
-    } else if constexpr (line_tiles(BM, MIGR)) {
-        if (!tg.line || p.gens != 1 || tg.w > tg.threads) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((line_kernel<SW, BM, APT, ASYNC>), dim3(tg.tiles), dim3(tg.threads),
-                           lds, stream, p);
+    } else if (tg.line) {
+        if constexpr (MIGR) {
+            if (p.gens != 1 || tg.w > tg.threads) return hipErrorInvalidValue;
+            hipLaunchKernelGGL((line_kernel<SW, BM, APT, ASYNC>), dim3(tg.tiles),
+                               dim3(tg.threads), lds, stream, p);
+        } else {
+            return hipErrorInvalidValue;
+        }
+    } else if constexpr (line_only(BM, MIGR)) {
+        return hipErrorInvalidValue;
     } else {
         // more generations than the emigrants around a tile reach
         if (p.gens > kTileGens && (MIGR || ASYNC)) return hipErrorInvalidValue;
@@ -1376,7 +1382,7 @@ hipError_t launch_batch_sites(const BatchRun* runs, uint32_t nruns, uint32_t max
 
 template <int SW, uint32_t BM, bool MIGR, int APT>
 __device__ __forceinline__ void step_batched(const StepParams& p, uint32_t tile) {
-    if constexpr (line_tiles(BM, MIGR)) step_line<SW, BM, APT, false>(p, tile);
+    if constexpr (line_only(BM, MIGR)) step_line<SW, BM, APT, false>(p, tile);
     else step_tile<SW, BM, MIGR, APT, false, false>(p, tile);
 }
 
