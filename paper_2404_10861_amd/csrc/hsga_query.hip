@@ -510,9 +510,11 @@ __global__ __launch_bounds__(kPairTileCols) void mrca_general_pairs_kernel(
 // most 2 S steps, one thread per pair and nothing to prepare.  A whole query,
 // merged and by tables: 4 sites 33.6 and 50.7 us for 1,919 annotations, 150
 // and 179 for 6,000; 8 sites 40.9 and 50.6, but 111 and 93 for 4,096; 32
-// sites 26.7 and 28.1 for 100, equal for 600; 64 sites 41.0 and 30.5 for 100.
+// sites 46.6 and 49.3 for 64, 53.3 and 61.0 for 513, 59.4 and 66.0 for 600,
+// equal at 768 (where the tables' workgroups take a fourth tile of columns), 87
+// and 73 for 900; 64 sites 41.0 and 30.5 for 100.
 inline bool merge_pairs(uint32_t S, uint32_t n) {
-    return S <= 4 || (S <= 8 && n < 3072) || (S <= 32 && n < 512);
+    return S <= 4 || (S <= 8 && n < 3072) || (S <= 32 && n < 768);
 }
 constexpr uint32_t kMergePairRows = 512;     // grid rows
 __global__ __launch_bounds__(256) void mrca_merge_pairs_kernel(
