@@ -142,9 +142,9 @@ struct RadiusRegisters {
 // sqrt(-2 ln U1).  1/sqrt q starts from a cubic instead of the
 // definition's 9/8 - 3q/16 and so takes three Newton steps where it takes
 // six: 12 instructions for 19, with the same result to the last bit for each
-// of the 2^32 radius words (compared one by one on this chip: sqrt q's
-// correction step squares what is left of the error, a rounding in either
-// case).  1/(m+1) keeps the definition's five steps from 1/2: they stop
+// of the 2^32 radius words (compared one by one, on this chip and, with
+// HSGA_ALL_WORDS=1, by tests/test_half_normal_words.py: sqrt q's correction
+// step squares what is left of the error, a rounding in either case).  1/(m+1) keeps the definition's five steps from 1/2: they stop
 // 1e-22 off at the ends, which the last rounding does see for a few words.
 template <class Coefficients>
 __device__ __forceinline__ double half_normal_radius(const Coefficients& K, uint32_t w_radius) {
