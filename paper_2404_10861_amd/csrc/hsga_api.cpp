@@ -516,10 +516,12 @@ int enqueue_steps(ga_run* r, const hsga::TileGeom& tile, uint32_t done, uint32_t
     const bool mig = r->cfg.migrants_per_island != 0;
     for (uint32_t k = 0; k < n; k += per) {
         const uint32_t gens = std::min(per, n - k);
-        // a launch of a single generation has nothing to gain from the islands
-        // around its tiles (16.8 M agents 75 us over tiles of two, 71 over a line;
-        // 96 k agents 4.7 and 3.9)
-        const bool single = mig && gens == 1 && !tile.whole && !tile.line;
+        // a synchronous launch of a single generation has nothing to gain from
+        // the islands around its tiles (1 M agents at 32 to an island stepped one
+        // by one 15.2 us over such tiles, 13.0 over a line; ticks of 16.8 M
+        // agents 105.1 and 107.9)
+        const bool single =
+            mig && gens == 1 && !tile.whole && !tile.line && r->cfg.async_activity == 0;
         const hsga::StepParams p = step_params(r, r->T + done + k, gens, r->cur, tau0,
                                                single ? line_tile(r, std::min(r->block, kMaxTileThreads)) : tile);
         hipError_t e = hsga::launch_step(p, r->SW, model, mig, r->apt, r->stream);

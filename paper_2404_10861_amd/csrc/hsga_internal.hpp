@@ -181,10 +181,11 @@ hipError_t launch_batch_sites(const BatchRun* runs, uint32_t nruns, uint32_t max
 // ceil((total_tiles - x) / kXcds) workgroups.
 // with_float: some run of the batch uses kBirthFloat (a separate kernel, so
 // that integer-only batches keep the integer kernel's register budget).
+// lines: every run's tile is a line (another one).
 constexpr uint32_t kXcds = 8;
 hipError_t launch_batch_step(const BatchRun* runs, const uint32_t* xcd_tab, uint32_t nruns,
                              uint32_t total_tiles, uint32_t k, uint32_t block_threads,
-                             size_t lds_bytes, bool with_float, hipStream_t stream);
+                             size_t lds_bytes, bool with_float, bool lines, hipStream_t stream);
 
 // Cut each of n runs' tiles (tiles[i], total T) into kXcds contiguous
 // chunks, one per XCD, that fill exactly XCD x's ceil((T - x) / kXcds)

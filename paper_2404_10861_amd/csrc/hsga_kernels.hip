@@ -1380,36 +1380,38 @@ hipError_t launch_batch_sites(const BatchRun* runs, uint32_t nruns, uint32_t max
     return hipGetLastError();
 }
 
-template <int SW, uint32_t BM, bool MIGR, int APT>
+template <int SW, uint32_t BM, bool MIGR, int APT, bool LINES>
 __device__ __forceinline__ void step_batched(const StepParams& p, uint32_t tile) {
-    if constexpr (line_only(BM, MIGR)) step_line<SW, BM, APT, false>(p, tile);
+    if constexpr (LINES || line_only(BM, MIGR)) step_line<SW, BM, APT, false>(p, tile);
     else step_tile<SW, BM, MIGR, APT, false, false>(p, tile);
 }
 
-template <int SW, uint32_t BM, bool MIGR>
+template <int SW, uint32_t BM, bool MIGR, bool LINES>
 __device__ __forceinline__ void step_tile_apt(const StepParams& p, uint32_t tile, uint32_t apt_log2) {
-    if (apt_log2 == 2) step_batched<SW, BM, MIGR, 4>(p, tile);
-    else if (apt_log2 == 1) step_batched<SW, BM, MIGR, 2>(p, tile);
-    else step_batched<SW, BM, MIGR, 1>(p, tile);
+    if (apt_log2 == 2) step_batched<SW, BM, MIGR, 4, LINES>(p, tile);
+    else if (apt_log2 == 1) step_batched<SW, BM, MIGR, 2, LINES>(p, tile);
+    else step_batched<SW, BM, MIGR, 1, LINES>(p, tile);
 }
 
-template <uint32_t BM>
+template <uint32_t BM, bool LINES>
 __device__ __forceinline__ void step_tile_variant(const StepParams& p, uint32_t tile,
                                                   uint32_t variant) {
     const uint32_t apt_log2 = (variant >> 4) & 3u;
-    const bool mig = (variant >> 3) & 1u;
+    const bool mig = LINES || ((variant >> 3) & 1u);
     if (variant & 1u) {
-        if (mig) step_tile_apt<2, BM, true>(p, tile, apt_log2);
-        else step_tile_apt<2, BM, false>(p, tile, apt_log2);
+        if (mig) step_tile_apt<2, BM, true, LINES>(p, tile, apt_log2);
+        else if constexpr (!LINES) step_tile_apt<2, BM, false, LINES>(p, tile, apt_log2);
     } else {
-        if (mig) step_tile_apt<1, BM, true>(p, tile, apt_log2);
-        else step_tile_apt<1, BM, false>(p, tile, apt_log2);
+        if (mig) step_tile_apt<1, BM, true, LINES>(p, tile, apt_log2);
+        else if constexpr (!LINES) step_tile_apt<1, BM, false, LINES>(p, tile, apt_log2);
     }
 }
 
 // WITH_FLOAT: the batch may hold float-treatment runs.  Integer-only
 // batches use the instantiation without them, which needs fewer registers.
-template <bool WITH_FLOAT>
+// LINES: every run steps over line tiles, one generation (a kernel of its
+// own: both forms' integer births in one made 64 batched runs 7 % slower).
+template <bool WITH_FLOAT, bool LINES>
 __global__ __launch_bounds__(1024) void batch_step_kernel(const BatchRun* __restrict__ runs,
                                                          const uint32_t* __restrict__ xcd_tab,
                                                          uint32_t nruns, uint32_t k) {
@@ -1440,7 +1442,7 @@ __global__ __launch_bounds__(1024) void batch_step_kernel(const BatchRun* __rest
     const uint32_t t = xcd_tab[(kXcds + x) * nruns + lo] + (j - pre[lo]);
     // (a constant where no run steps otherwise: read from the table it would
     // be one more wait before the tile's loads, 2 % of 64 batched runs)
-    const uint32_t per = WITH_FLOAT ? R.tile.draws : kTileGens;
+    const uint32_t per = LINES ? 1u : WITH_FLOAT ? R.tile.draws : kTileGens;
     if (k * per >= R.gens) return;
     const uint32_t g = R.T0 + k * per;
     const uint32_t src = k & 1u, dst = src ^ 1u;
@@ -1477,21 +1479,24 @@ __global__ __launch_bounds__(1024) void batch_step_kernel(const BatchRun* __rest
     p.del_thr = R.del_thr; p.ben_thr = R.ben_thr;
     p.del_scale = -(double)R.del_sigma; p.ben_scale = R.ben_sigma;
     const uint32_t model = (R.variant >> 1) & 3u;
-    if (model == kBirthIntTournament) step_tile_variant<kBirthIntTournament>(p, t, R.variant);
-    else if (WITH_FLOAT && model == kBirthFloat) step_tile_variant<kBirthFloat>(p, t, R.variant);
-    else step_tile_variant<kBirthIntNeutral>(p, t, R.variant);
+    if (model == kBirthIntTournament)
+        step_tile_variant<kBirthIntTournament, LINES>(p, t, R.variant);
+    else if (WITH_FLOAT && model == kBirthFloat)
+        step_tile_variant<kBirthFloat, LINES>(p, t, R.variant);
+    else
+        step_tile_variant<kBirthIntNeutral, LINES>(p, t, R.variant);
 }
 
 hipError_t launch_batch_step(const BatchRun* runs, const uint32_t* xcd_tab, uint32_t nruns,
                              uint32_t total_tiles, uint32_t k, uint32_t block_threads,
-                             size_t lds_bytes, bool with_float, hipStream_t stream) {
+                             size_t lds_bytes, bool with_float, bool lines,
+                             hipStream_t stream) {
     if (nruns == 0 || total_tiles == 0) return hipSuccess;
-    if (with_float)
-        hipLaunchKernelGGL(batch_step_kernel<true>, dim3(total_tiles), dim3(block_threads),
-                           lds_bytes, stream, runs, xcd_tab, nruns, k);
-    else
-        hipLaunchKernelGGL(batch_step_kernel<false>, dim3(total_tiles), dim3(block_threads),
-                           lds_bytes, stream, runs, xcd_tab, nruns, k);
+    const auto kernel = lines        ? &batch_step_kernel<true, true>
+                        : with_float ? &batch_step_kernel<true, false>
+                                     : &batch_step_kernel<false, false>;
+    hipLaunchKernelGGL(kernel, dim3(total_tiles), dim3(block_threads), lds_bytes, stream, runs,
+                       xcd_tab, nruns, k);
     return hipGetLastError();
 }
 

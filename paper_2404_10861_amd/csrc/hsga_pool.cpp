@@ -48,10 +48,10 @@ constexpr uint64_t kSplitWords = 1u << 22;
 struct Group {
     uint32_t first = 0, count = 0, tiles = 0;
     size_t lds = 0;
-    bool with_float = false;
+    bool with_float = false, lines = true;
     bool operator==(const Group& o) const {
         return first == o.first && count == o.count && tiles == o.tiles && lds == o.lds &&
-               with_float == o.with_float;
+               with_float == o.with_float && lines == o.lines;
     }
 };
 
@@ -175,7 +175,8 @@ hipStream_t stream_of(const ga_pool* p, uint32_t q) { return q ? p->side[q - 1] 
 hipError_t launch_group(ga_pool* p, const GraphKey& key, uint32_t q, uint32_t k) {
     const Group& g = key.grp[q];
     return hsga::launch_batch_step(p->d_table + g.first, p->d_xtab + xcd_words(g.first), g.count,
-                                   g.tiles, k, p->block, g.lds, g.with_float, stream_of(p, q));
+                                   g.tiles, k, p->block, g.lds, g.with_float, g.lines,
+                                   stream_of(p, q));
 }
 
 // Group q's launches of every generation, captured on its stream into
@@ -394,6 +395,14 @@ int ga_pool_advance(ga_pool* p, uint32_t max_gens, uint32_t* gens_enqueued) {
     key.block = p->block;
     const uint32_t nruns = (uint32_t)active.size();
     std::vector<uint32_t> run_tiles(nruns);
+    // an advance by one generation takes line tiles, if every run can (a launch
+    // takes one form of integer births)
+    bool single = true;
+    for (uint32_t s : active) {
+        const ga_run& r = p->slots[s].run;
+        single = single && std::min(G, p->slots[s].target - r.T) == 1 &&
+                 r.cfg.migrants_per_island != 0;
+    }
     uint64_t words_before = 0;
     for (uint32_t i = 0; i < nruns; ++i) {
         Slot& s = p->slots[active[i]];
@@ -405,7 +414,7 @@ int ga_pool_advance(ga_pool* p, uint32_t max_gens, uint32_t* gens_enqueued) {
         Group& grp = key.grp[q];
         r.block = p->block;
         const uint32_t g = std::min(G, s.target - r.T);
-        hsga::TileGeom tile = run_tile(&r, p->block);
+        hsga::TileGeom tile = single ? line_tile(&r, p->block) : run_tile(&r, p->block);
         tile.threads = (uint16_t)p->block;
         const hsga::StepParams sp = step_params(
             &r, r.T, g, r.cur, hsga::ingests_of(r.T, r.cfg.ingest_interval), tile);
@@ -434,6 +443,7 @@ int ga_pool_advance(ga_pool* p, uint32_t max_gens, uint32_t* gens_enqueued) {
         b.interval = r.cfg.ingest_interval;
         b.diff_log2 = sp.diff_log2;
         b.tile = tile;
+        grp.lines = grp.lines && tile.line != 0;
         const uint32_t rt = tile.tiles;
         run_tiles[i] = rt;
         grp.tiles += rt;

@@ -69,3 +69,35 @@ def test_large_runs_on_both_sides_of_the_rule(orc, w, h, n, sites, activity, sha
     cfg = hs.Config(w, h, n, sites, "steady", seed=n, tournament_size=2,
                     async_activity=P(activity))
     check(orc, cfg, (3, 4), shape)
+
+
+def test_pool_advanced_one_by_one(orc):
+    """A pool's advances of one generation (line tiles, if every run has
+    migration) between longer ones."""
+    import paper_2404_10861_amd as hs
+    cfgs = [hs.Config(13, 10, 32, 64, "tilted", seed=1, tournament_size=2),
+            hs.Config(45, 7, 3, 32, "steady", seed=2, tournament_size=0),
+            hs.Config(9, 9, 6, 64, "hybrid", seed=3, fitness_model="float", tournament_size=5,
+                      del_threshold=P(0.33), ben_threshold=P(0.03)),
+            hs.Config(8, 5, 32, 32, "tilted", seed=4, migrants_per_island=0, tournament_size=2)]
+    for n in (3, 4):
+        need = sum((hs.footprint_bytes(c, 8) + 255) & ~255 for c in cfgs[:n])
+        pool = hs.Pool(need + hs.pool_overhead_bytes(n) + (1 << 20), max_runs=n,
+                       max_gens_per_launch=8, block_threads=128)
+        ids = [pool.admit(c, 1000) for c in cfgs[:n]]
+        for g in (1, 1, 3, 1, 8, 1, 1, 1):
+            pool.advance(g)
+        pool.sync()
+        for i, cfg in zip(ids, cfgs):
+            ref = orc.Run(cfg.grid_w, cfg.grid_h, cfg.pop_per_island, cfg.surface_sites, cfg.kind,
+                          tournament=cfg.tournament_size, mut_thr=cfg.mut_threshold,
+                          mut_lo=cfg.mut_lo, mut_hi=cfg.mut_hi, migrants=cfg.migrants_per_island,
+                          seed=cfg.seed, fitness_model={"int": 0, "float": 1}[cfg.fitness_model],
+                          del_thr=cfg.del_threshold, ben_thr=cfg.ben_threshold,
+                          del_sigma=cfg.del_sigma, ben_sigma=cfg.ben_sigma)
+            ref.step(17)
+            run = pool.run(i)
+            for got, want in zip(run.agents(), ref.agents()):
+                assert np.array_equal(got, want)
+            for got, want in zip(run.outbox() or (), ref.outbox() or ()):
+                assert np.array_equal(got, want)
