@@ -1198,11 +1198,15 @@ __device__ __forceinline__ void step_line(const StepParams& p, uint32_t tile) {
     // this thread's island and first slot (one division: la0 < 4096), and its
     // birth draws while the loads are in flight (a float birth's two blocks
     // an agent would cost a wave per SIMD here)
-    const uint32_t lil = (la0 * p.tile.n_magic) >> 20;
-    const uint32_t j0 = la0 - lil * N, isl = first + lil;
+    auto place = [&](uint32_t la, uint32_t& il, uint32_t& j) {
+        il = (la * p.tile.n_magic) >> 20;
+        j = la - il * N;
+    };
+    uint32_t lil, j0;
+    place(la0, lil, j0);
     BirthDraws<BM, APT> draws;
     if constexpr (BM != kBirthFloat)
-        if (mine) draws.compute(key, j0, isl, p.g);
+        if (mine) draws.compute(key, j0, first + lil, p.g);
     // 2. stage the tile, then the immigrants over the drawn slots (north,
     // south, west, east: a later direction overwrites an earlier one)
     if (mine) {
@@ -1228,6 +1232,14 @@ __device__ __forceinline__ void step_line(const StepParams& p, uint32_t tile) {
     __syncthreads();
     // 3. births
     if (!mine) return;
+    // (the thread's place is worked out again: kept across the barriers it would
+    // cost tournaments on two-word surfaces the eighth wave per SIMD, and runs
+    // of 2^21 agents, just eight waves on every SIMD, a second round: 14.4 ->
+    // 12.5 us per generation at four agents to an island)
+    uint32_t la = la0;
+    asm volatile("" : "+v"(la));
+    place(la, lil, j0);
+    const uint32_t isl = first + lil;
     const uint32_t emig = l_emig[lil], base = lil * N;
     Children<SW, APT> kid;
     if (ASYNC && (emig >> 8) == 4u) {
