@@ -13,7 +13,8 @@ Prints one JSON line:
             synchronous generations staged on the chip must move) over its
             average launch duration (HIP events on the run's stream);
             traffic: the HBM bytes per launch that rocprofv3 counted for
-            the same code (profiles/), null once the code has changed
+            the same code (profiles/), null once the code has changed;
+            bound: VALU issue or HBM, whichever the step is nearer to
   cpu_baseline  the plain C oracle on a bounded sample of the same
             workload (the first generations from the founders).
 
@@ -39,6 +40,7 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, 8 TB/s
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "step_kernel_c2_traffic.json")
+TRAFFIC_TWO_FILE = os.path.join(ROOT, "profiles", "step_kernel_c2_two_generations_traffic.json")
 SQ_FILE = os.path.join(ROOT, "profiles", "step_kernel_c2_sq_counters.json")
 
 
@@ -79,15 +81,17 @@ def batch_bytes_per_generation(spec) -> int:
 
 def measured_traffic(spec):
     """HBM bytes per step launch from the committed rocprofv3 counter
-    summary, or None when it is absent or the kernel changed since."""
-    if not os.path.exists(TRAFFIC_FILE):
-        return None
-    with open(TRAFFIC_FILE) as f:
-        rec = json.load(f)
+    summaries (launches of one generation and of two): the one taken with
+    this code, or None when there is none or the kernel changed since."""
     from paper_2404_10861_amd.profiling import kernel_hash
-    if rec.get("kernel_hash") != kernel_hash():
-        return None
-    return rec.get("bytes_per_launch")
+    for path in (TRAFFIC_TWO_FILE, TRAFFIC_FILE):
+        if not os.path.exists(path):
+            continue
+        with open(path) as f:
+            rec = json.load(f)
+        if rec.get("kernel_hash") == kernel_hash():
+            return rec.get("bytes_per_launch")
+    return None
 
 
 def measured_valu():
@@ -376,13 +380,14 @@ def main(argv=None) -> int:
             if gen_us:
                 gbs = bytes_gen / (gen_us * 1e-6) / 1e9
                 res["roofline"] = {
-                    "bound": "hbm", "achieved": gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+                    "bound": "valu", "achieved": gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                     "frac": gbs / HBM_PEAK_GBS, "frac_of_attainable": gbs / copy_gbs,
                     "kernel": "batch_step_kernel, the launch groups side by side",
                     "generation_us": gen_us,
                     "note": "achieved: the set's algorithmic bytes per generation over the "
                             "wall time per generation after tuning (HIP events on the "
-                            "pool's stream)"}
+                            "pool's stream), peak and frac of HBM; VALU issue is nearer its "
+                            "limit (profiles/batched_c4_sq_counters.md)"}
             metric = "agent-replications/sec (batched vs sequential plain)"
             value = res["batched_replications_per_s"]
         else:
@@ -460,6 +465,9 @@ def main(argv=None) -> int:
     avg_launch_s = kern_ms / 1000.0 / max(launches, 1) * GENS_PER_LAUNCH
     achieved_gbs = bytes_per_launch / avg_launch_s / 1e9
     traffic = measured_traffic(spec)
+    valu = measured_valu()
+    # the resource nearer its limit (the bytes' if the kernel has no counters)
+    valu_bound = valu is not None and valu["issue_estimate"] > achieved_gbs / HBM_PEAK_GBS
     line = {
         "metric": "agent-replications/sec",
         "value": value,
@@ -485,7 +493,7 @@ def main(argv=None) -> int:
             "seed": spec.seed,
         },
         "roofline": {
-            "bound": "hbm",
+            "bound": "valu" if valu_bound else "hbm",
             "achieved": achieved_gbs,
             "peak": HBM_PEAK_GBS,
             "unit": "GB/s",
@@ -498,18 +506,19 @@ def main(argv=None) -> int:
             "bytes_per_replication": bytes_per_launch / spec.agents / GENS_PER_LAUNCH,
             "attainable_copy_GBs": copy_gbs,
             "frac_of_attainable": achieved_gbs / copy_gbs,
-            "note": "algorithmic bytes: 12-byte records (trait, 64 one-bit sites; every "
-                    "counter is the generation number) read and written, and one 16-byte "
-                    "migrant entry written and read per island, once for the two "
-                    "generations of a launch (VALU issue, not bandwidth, is then the nearer "
-                    "bound); record_model_* prices a stored counter and 32-byte entries, "
-                    "which this step does not move",
+            "note": "achieved, peak and frac are of HBM bytes, whatever the bound (valu: its "
+                    "issue_estimate is the fraction); algorithmic bytes: 12-byte records "
+                    "(trait, 64 one-bit sites; every counter is the generation number) read "
+                    "and written, and one 16-byte migrant entry written and read per "
+                    "island, once for the two generations of a launch; record_model_* "
+                    "prices a stored counter and 32-byte entries, which this step does not "
+                    "move",
             "record_model_bytes_per_launch": record_bytes,
             "record_model_GBs": record_bytes / avg_launch_s / 1e9,
             "traffic_GBs": traffic / avg_launch_s / 1e9 if traffic else None,
             "traffic_frac_of_attainable":
                 traffic / avg_launch_s / 1e9 / copy_gbs if traffic else None,
-            "valu": measured_valu(),
+            "valu": valu,
         },
         "context": {
             "paper_cs2_replications_per_s": 3.18e11,

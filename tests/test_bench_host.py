@@ -57,6 +57,20 @@ def test_traffic_is_reported_only_for_the_profiled_code(monkeypatch):
     assert bench.measured_traffic(wl.c2()) is None
 
 
+def test_traffic_of_the_two_generation_launches(monkeypatch):
+    """The figure of launches that step two generations: the bytes such a
+    launch must move and the records read around its tiles, at most a tenth
+    more; reported for the code it was taken with."""
+    import bench
+    from paper_2404_10861_amd import profiling
+    from paper_2404_10861_amd import workloads as wl
+    with open(bench.TRAFFIC_TWO_FILE) as f:
+        rec = json.load(f)
+    assert 1 <= rec["bytes_per_launch"] / bench.algorithmic_bytes_per_generation(wl.c2()) < 1.1
+    monkeypatch.setattr(profiling, "kernel_hash", lambda sources=None: rec["kernel_hash"])
+    assert bench.measured_traffic(wl.c2()) == rec["bytes_per_launch"]
+
+
 def test_valu_is_reported_only_for_the_profiled_code(monkeypatch):
     import bench
     from paper_2404_10861_amd import profiling
