@@ -6,8 +6,9 @@ Two knobs shape a pool's launches without changing any result:
   block_threads * agents_per_thread / N whole islands, so the tile is set
   by the workgroup size (64, 128 or 256 threads);
 * generations per launch: how many generations one advance enqueues (one
-  site-schedule launch plus one step launch per two generations, replayed as a
-  captured hipGraph or launched directly).
+  site-schedule launch plus one step launch per two generations, or per one
+  where a run has float births, replayed as a captured hipGraph
+  or launched directly).
 
 Because results do not depend on either knob, tuning runs online: each
 candidate shape advances the real runs once, the wall time per generation

@@ -148,7 +148,8 @@ hipError_t launch_set_layout(uint32_t* layout, const uint32_t* words, uint32_t S
 // generation per launch was bound by that traffic.  Paper-scale run (16.8 M
 // agents, two-word surfaces): 70.5 us per generation with one a launch (5.9
 // TB/s, 415 VALU instructions per wavefront), 45.8 us with two (357 per
-// generation, 79 % of VALU issue; a float trial's generation 98 %).
+// generation, 80 % of VALU issue).  Float births with migration, and integer
+// runs whose islands around a tile are many for its agents, take step_line.
 //  1. Each thread issues one 16-byte (APT = 4) non-temporal load per plane
 //     for its APT consecutive agents: traits and surface words, counters
 //     only for asynchronous ticks (in a synchronous run every counter is the

@@ -29,9 +29,9 @@ struct Slot {
 
 // An advance cuts the active runs, in table order, into kGroups
 // contiguous groups of about equal bytes per generation and gives each
-// group one launch per two generations (or one) on a stream of its own.  The groups'
-// runs are independent, so the streams run side by side and one group's
-// launch tail (its last, partly filled wave of workgroups, and the gap
+// group one launch per two generations (per one where a run has float
+// births, or where the advance is of one) on a stream of its own.  The groups' runs are
+// independent, so the streams run side by side and one group's launch tail (its last, partly filled wave of workgroups, and the gap
 // before its next launch) overlaps the others' work.  Only generations
 // that read at least kSplitWords trait and surface words are split: below
 // that a launch is short, its tail small, and the second launch per
