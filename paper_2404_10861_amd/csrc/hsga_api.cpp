@@ -268,7 +268,6 @@ hsga::TileGeom make_tile(const ga_run* r, uint32_t w, uint32_t h, bool whole) {
     t.w = (uint16_t)w;
     t.h = (uint16_t)h;
     t.cols = (uint16_t)((r->cfg.grid_w + w - 1) / w);
-    t.tiles = t.cols * ((r->cfg.grid_h + h - 1) / h);
     t.threads = (uint16_t)((w * h * (r->N / r->apt) + 63) / 64 * 64);
     t.whole = whole ? 1 : 0;
     t.n_magic = ((1u << 20) + r->N - 1) / r->N;
@@ -294,7 +293,6 @@ hsga::TileGeom make_line(const ga_run* r, uint32_t islands, uint32_t threads) {
     t.threads = (uint16_t)threads;
     t.line = 1;
     t.draws = 1;
-    t.tiles = (r->I + islands - 1) / islands;
     t.n_magic = ((1u << 20) + r->N - 1) / r->N;
     uint32_t shift;
     hsga::column_magic(r->cfg.grid_w, &t.cols_magic, &shift);
@@ -341,7 +339,7 @@ const hsga::TileGeom& run_tile(ga_run* r, uint32_t block) {
             t = make_tile(r, --w, h, false);
         if (2 * (w + h) > t.threads || tile_lds(r, t) > kMaxStepLds) break;
         const uint64_t lanes = t.threads * r->apt + (uint64_t)(w + h) * r->N / 2;
-        const uint64_t cost = lanes * t.tiles;
+        const uint64_t cost = lanes * hsga::tile_count(t, W, H);
         if (cost < best) {
             best = cost;
             r->tile = t;

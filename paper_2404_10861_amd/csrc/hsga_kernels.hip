@@ -1317,7 +1317,7 @@ static hipError_t launch_step_t(const StepParams& p, hipStream_t stream) {
     } else if (tg.line) {
         if constexpr (MIGR) {
             if (p.gens != 1 || tg.w > tg.threads) return hipErrorInvalidValue;
-            hipLaunchKernelGGL((line_kernel<SW, BM, APT, ASYNC>), dim3(tg.tiles),
+            hipLaunchKernelGGL((line_kernel<SW, BM, APT, ASYNC>), dim3(tile_count(tg, p.W, p.H)),
                                dim3(tg.threads), lds, stream, p);
         } else {
             return hipErrorInvalidValue;
@@ -1328,7 +1328,7 @@ static hipError_t launch_step_t(const StepParams& p, hipStream_t stream) {
         // more generations than the emigrants around a tile reach
         if (p.gens > kTileGens && (MIGR || ASYNC)) return hipErrorInvalidValue;
         if (2u * (tg.w + tg.h) > tg.threads) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((step_kernel<SW, BM, MIGR, APT, ASYNC>), dim3(tg.tiles),
+        hipLaunchKernelGGL((step_kernel<SW, BM, MIGR, APT, ASYNC>), dim3(tile_count(tg, p.W, p.H)),
                            dim3(tg.threads), lds, stream, p);
     }
     return hipGetLastError();

@@ -444,7 +444,7 @@ int ga_pool_advance(ga_pool* p, uint32_t max_gens, uint32_t* gens_enqueued) {
         b.diff_log2 = sp.diff_log2;
         b.tile = tile;
         grp.lines = grp.lines && tile.line != 0;
-        const uint32_t rt = tile.tiles;
+        const uint32_t rt = hsga::tile_count(tile, r.cfg.grid_w, r.cfg.grid_h);
         run_tiles[i] = rt;
         grp.tiles += rt;
         ++grp.count;
