@@ -1098,7 +1098,8 @@ __host__ __device__ inline LineLds line_lds(uint32_t islands, uint32_t N, uint32
 // generation's emigrants from around the tile, few lanes of a wave with a
 // half-normal each, make 958 VALU instructions per wavefront and generation
 // of 828 (18 M agents, tournament of five: 112.4 us per generation in
-// launches of two, 105.2 here; one-word surfaces 107.3 and 97.2; ticks of
+// launches of two, 105.2 here, or 112.9 and 111.9 on a card that holds a lower
+// clock under this load; one-word surfaces 107.3 and 97.2; ticks of
 // 8.4 M agents 71.6 and 68.4).  A run below half a million agents is bound
 // by its chain of latencies instead: the arguments' cache lines are asked for
 // at once, the coefficients' while the planes are on their way, and the
